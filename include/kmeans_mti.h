@@ -196,11 +196,16 @@ int kmeans_mti_run(const float* X, int64_t n, int32_t d, int32_t k, const float*
  * followed by k_small_finish, with KM_FLAG_FULL_SUMS or KM_FLAG_STATS),
  * "lds-vector" /
  * "lds-mfma" (centroids and sums in LDS: k_assign with vector or matrix-core
- * survivors, then k_reduce, k_update, k_centroid_table), "lds-inc" (d = 16
- * or 32, k <= 128, where the streaming path does not apply: k_inc_mm reads
- * the point states and only the Clause-1 survivors' rows, settles the
- * survivors on the matrix cores and sums the moves of the points whose
- * cluster changed; then k_reduce, k_update, k_centroid_table), "lds-elkan" (the
+ * survivors, then k_reduce, k_update, k_centroid_table; "lds-vector" without
+ * a flag that asks for the general kernel or for full sums is k_inc_vec,
+ * d <= 16 and few centroids: only the point states and the Clause-1
+ * survivors' rows are read, one lane per survivor; then k_update,
+ * k_centroid_table), "lds-inc" (only the states and the survivors' rows are
+ * read, the survivors are settled on the matrix cores and the moves of the
+ * points whose cluster changed are summed: k_inc_mm for d = 16 or 32 and k <=
+ * 128, then k_reduce, k_update, k_centroid_table; k_inc_mat for other d and k
+ * <= 256 while its tables fit in LDS, then k_update, k_centroid_table),
+ * "lds-elkan" (the
  * same with KM_FLAG_ELKAN's lower-bound scan), "global-mfma"
  * (centroids or sums too large for LDS: dense MFMA survivors, sums by
  * counting sort).  "" for a NULL context.

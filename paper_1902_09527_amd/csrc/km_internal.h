@@ -44,6 +44,9 @@ struct IterState {
     // Fixed-point scales (set-up kernel k_set_scales, from the largest |x|):
     // 2^S, 2^-S of the coordinate sums and the same for the inertia sum.
     double qscale, qinv, iscale, iinv;
+    // Scale 2^a of the f16 operands and 2^-a (k_set_scales): the sample's
+    // bound on |x| and the largest |c| of C0 map to at most 2^13.
+    float xscale, xinv;
     // Nullable: a pinned, coherent host word that the end of every step sets
     // to the steps ended, negated once the stop test is met (a run's host
     // loop polls it instead of copying the flag).
@@ -72,6 +75,7 @@ struct Dev {
     uint32_t* w;          // incremental path: point states (cluster and bound, below), padded
     uint64_t* sums;       // incremental path: k*d + k exact sums and counts, carried across steps (else null)
     float* hm;            // incremental path: k x 4, min over centroid block cb of h[a][j] (h[a][a] = 0), else null
+    uint64_t* rows;       // general incremental path: kGenRows x L accumulation rows (zero between steps), else null
     uint64_t* part;       // G x L per-block partial rows
     uint64_t* total;      // L reduced row (zero between iterations)
     IterState* st;
@@ -396,7 +400,7 @@ hipError_t launch_absmax(const float* a, int64_t na, const float* b, int64_t nb,
 
 // Buffers cleared and the loop state written by one set-up launch.
 struct ZeroRanges {
-    static constexpr int kMax = 16;
+    static constexpr int kMax = 20;
     void* p[kMax];        // 16-byte aligned
     uint64_t bytes[kMax]; // multiples of 4
     int32_t n;
@@ -501,6 +505,92 @@ const void* inc_mm_symbol(int d, int k);
 hipError_t launch_inc_mm(const Dev& dv, int grid, int lds_bytes, int first, hipStream_t s);
 // assign_out[i] = cluster of point i from the point states.
 hipError_t launch_inc_mm_unpack(const Dev& dv, int32_t* assign_out, hipStream_t s);
+
+// General incremental steps (km_gen.hip): any d, the widths and cluster
+// counts for which the tables, the exact sums and the waves' lists fit in LDS.
+constexpr int kGenWaves = 8;          // waves per block
+constexpr int kGenThreads = 64 * kGenWaves;
+constexpr int kGenTile = 256;         // most points a wave takes at once (64, 128 or 256); the state array is padded to it
+constexpr int kGenRows = 16;          // accumulation rows
+constexpr int kGenVecMaxD = 16, kGenVecMaxK = 64, kGenVecMaxKD = 256;   // one lane per survivor up to here
+constexpr int kGenVecQ = 128;         // survivor queue of a wave: one batch of 64 and one sub-step of 64 points
+constexpr int kGenMatMaxK = 256, kGenMatMaxD = 1024;
+
+enum GenKind { kGenNone = 0, kGenVec = 1, kGenMat = 2 };
+
+struct GenVecLds {
+    int off_c, off_h, off_thr, off_s, off_ec, off_ddn, off_acc, off_cnt, off_misc, off_q, off_m, ar, bytes;
+};
+__host__ __device__ inline GenVecLds gen_vec_lds(int DP, int d, int k) {
+    GenVecLds L;
+    int o = 0;
+    auto take = [&](int bytes) {
+        o = (o + 15) / 16 * 16;
+        int r = o;
+        o += bytes;
+        return r;
+    };
+    L.ar = d | 1;   // odd stride (uint64) of a cluster's sums: clusters on different banks
+    const int ks = (k + 3) / 4 * 4;
+    L.off_c = take(4 * ks * DP);
+    L.off_h = take(4 * k * ks);
+    L.off_thr = take(4 * k);
+    L.off_s = take(4 * k);
+    L.off_ec = take(4 * k);
+    L.off_ddn = take(4 * k);
+    L.off_acc = take(8 * k * L.ar);
+    L.off_cnt = take(4 * k);
+    L.off_misc = take(64);   // tile counter at 0, kNumStat uint64 counters at 16
+    L.off_q = take(kGenWaves * kGenVecQ * 8);
+    L.off_m = take(kGenWaves * 64 * 8);
+    L.bytes = (o + 15) / 16 * 16;
+    return L;
+}
+
+// One wave's lists of the matrix-core form.  Survivors with several
+// candidates are listed with up to kGenCand of them (more: all centroids) and
+// decided once kGenList of them or kGenPairs (survivor, candidate) pairs wait.
+constexpr int kGenCand = 6, kGenList = 32, kGenPairs = 128;
+struct GenMatWave {
+    uint2 q[96];          // survivors (point, state): one batch of 32 short of full and a sub-step of 64 points
+    uint2 ml[64];         // moves being applied
+    uint2 lq[kGenList + 32];                       // listed survivors
+    uint32_t lo[kGenList + 32];                    // first pair of each, their number << 16 (0: all centroids)
+    float pd[kGenPairs + 32 * kGenCand];           // the pairs' distances
+    uint16_t pl[kGenPairs + 32 * kGenCand];        // the pairs: listed survivor << 8 | centroid
+};
+struct GenMatLds {
+    int off_ca, off_nb, off_thr, off_ec, off_ddn, off_acc, off_cnt, off_misc, off_w, ar, bytes;
+};
+__host__ __device__ inline GenMatLds gen_mat_lds(int KB, int d, int k) {
+    GenMatLds L;
+    int o = 0;
+    auto take = [&](int bytes) {
+        o = (o + 15) / 16 * 16;
+        int r = o;
+        o += bytes;
+        return r;
+    };
+    L.ar = d | 1;
+    L.off_ca = take((d + 15) / 16 * KB * 2048);
+    L.off_nb = take(4 * 32 * KB);
+    L.off_thr = take(4 * k);
+    L.off_ec = take(4 * k);
+    L.off_ddn = take(4 * k);
+    L.off_acc = take(8 * k * L.ar);
+    L.off_cnt = take(4 * k);
+    L.off_misc = take(64);
+    L.off_w = take(kGenWaves * (int)sizeof(GenMatWave));
+    L.bytes = (o + 15) / 16 * 16;
+    return L;
+}
+
+// Which form takes (n, d, k), if any; its LDS bytes, symbol and launch.
+GenKind gen_kind(int64_t n, int d, int k, int max_lds);
+int gen_lds_bytes(GenKind kind, int d, int k);
+const void* gen_symbol(GenKind kind, const Dev& dv);
+hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, int first, hipStream_t s);
+hipError_t launch_gen_unpack(GenKind kind, const Dev& dv, int32_t* assign_out, hipStream_t s);
 
 // k-means++ seeding (km_pp.hip).  Points are processed in chunks of
 // kPPChunk rows, one workgroup per chunk; the block weight sums are per chunk.

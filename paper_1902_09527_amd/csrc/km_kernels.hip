@@ -190,7 +190,13 @@ __global__ __launch_bounds__(256) void k_init_buffers(ZeroRanges z) {
 // the bound).
 __global__ void k_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d, int unit) {
     if (threadIdx.x != 0) return;
-    put_scales(st, sum_exp(absmax), unit ? 1.0f : __uint_as_float(absmax[kAmaxC]), n, d);
+    const float cmax = unit ? 1.0f : __uint_as_float(absmax[kAmaxC]);
+    put_scales(st, sum_exp(absmax), cmax, n, d);
+    const int es = bound_exp((double)__uint_as_float(absmax[kAmaxSample])) + 4, ec = bound_exp((double)cmax);
+    int a = 13 - (es > ec ? es : ec);
+    a = a > 100 ? 100 : (a < -100 ? -100 : a);
+    st->xscale = ldexpf(1.f, a);
+    st->xinv = ldexpf(1.f, -a);
 }
 
 __global__ void k_set_centroids(const float* __restrict__ C0, double* C64, float* C32, float* ec,
@@ -249,61 +255,72 @@ __global__ void k_set_centroids_unit(const float* __restrict__ C0, double* C64, 
 // h[i][j] (paper section III-C, with the factor 1/2 of Elkan's lemma), and
 // ec_max for the recheck band.  One block per row i.
 
+// What bounds it is the latency of one block per row: the row's distances are
+// spread over the whole block, G lanes per distance (G a power of two, at
+// most 16, so that one distance is a few loads deep and the loads of a group
+// are coalesced), and the norm and the minima are formed by a wave each.  One
+// lane per distance and a serial norm took 12.9 us at k = 50, d = 64 (38.8 us
+// at k = 10, d = 174); this form takes 6.2 us (5.6 us).
+
 __global__ __launch_bounds__(256) void k_centroid_table(Dev P, int force) {
     if (!force && !P.st->active) return;
-    const int i = blockIdx.x, k = P.k, d = P.d;
+    const int i = blockIdx.x, k = P.k, d = P.d, tid = threadIdx.x, lane = tid & 63;
     const double* ci = P.C64 + (int64_t)i * d;
+    __shared__ float hrow[kIMMaxK], red[4], redm[4];
+    const int G = d <= 4 ? 1 : d <= 8 ? 2 : d <= 16 ? 4 : d <= 32 ? 8 : 16;
+    const int g = tid & (G - 1);
     float mn = INFINITY;
-    for (int j = threadIdx.x; j < k; j += blockDim.x) {
-        float hv = 0.f;
-        if (j != i) {
+    for (int j0 = 0; j0 < k; j0 += 256 / G) {   // whole groups take part (shuffles below)
+        const int j = j0 + tid / G;
+        double acc = 0.0;
+        if (j < k) {
             const double* cj = P.C64 + (int64_t)j * d;
-            double acc = 0.0;
-            for (int m = 0; m < d; ++m) {
-                double t = ci[m] - cj[m];
+#pragma unroll 4
+            for (int m = g; m < d; m += G) {
+                const double t = ci[m] - cj[m];
                 acc = fma(t, t, acc);
             }
+        }
+        for (int o = 1; o < G; o <<= 1) acc += __shfl_xor(acc, o);
+        if (j < k && g == 0) {
             // float64 rounding of the sum and the square root stays far below 2^-40
-            hv = f32_down(0.5 * sqrt(acc) * (1.0 - 0x1p-40));
-            mn = fminf(mn, hv);
-        }
-        P.h[(int64_t)i * k + j] = hv;
-    }
-    if (P.hm) {   // incremental path (k <= 128): min of row i over each 32-centroid block
-        __shared__ float hrow[kIMMaxK];
-        for (int j = threadIdx.x; j < k; j += blockDim.x) hrow[j] = P.h[(int64_t)i * k + j];
-        __syncthreads();
-        if ((int)threadIdx.x < 4) {
-            const int cb = threadIdx.x, j1 = min(32 * cb + 32, k);
-            float m = INFINITY;
-            for (int j = 32 * cb; j < j1; ++j) m = fminf(m, hrow[j]);   // h[i][i] = 0
-            P.hm[4 * i + cb] = m;
+            const float hv = j == i ? 0.f : f32_down(0.5 * sqrt(acc) * (1.0 - 0x1p-40));
+            if (j != i) mn = fminf(mn, hv);
+            P.h[(int64_t)i * k + j] = hv;
+            if (P.hm) hrow[j] = hv;
         }
     }
-    if (threadIdx.x == 0) {   // ||c32_i||^2 for the expansion form of the matrix-core path
-        const float* c = P.C32 + (int64_t)i * d;
-        double n2 = 0.0;
-        for (int m = 0; m < d; ++m) n2 = fma((double)c[m], (double)c[m], n2);
-        P.cn2[i] = (float)n2;
-    }
-    __shared__ float red[256];
-    __shared__ float redm[256];
-    red[threadIdx.x] = mn;
     float em = 0.f;
     if (i == 0)
-        for (int j = threadIdx.x; j < k; j += blockDim.x) em = fmaxf(em, P.ec[j]);
-    redm[threadIdx.x] = em;
-    __syncthreads();
-    for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            red[threadIdx.x] = fminf(red[threadIdx.x], red[threadIdx.x + w]);
-            redm[threadIdx.x] = fmaxf(redm[threadIdx.x], redm[threadIdx.x + w]);
-        }
-        __syncthreads();
+        for (int j = tid; j < k; j += 256) em = fmaxf(em, P.ec[j]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        mn = fminf(mn, __shfl_xor(mn, o));
+        em = fmaxf(em, __shfl_xor(em, o));
     }
-    if (threadIdx.x == 0) {
-        P.s[i] = red[0];
-        if (i == 0) P.st->ec_max = redm[0];
+    if (lane == 0) {
+        red[tid >> 6] = mn;
+        redm[tid >> 6] = em;
+    }
+    __syncthreads();
+    if (tid < 64) {   // ||c32_i||^2 for the expansion form of the matrix-core paths
+        const float* c = P.C32 + (int64_t)i * d;
+        double n2 = 0.0;
+        for (int m = lane; m < d; m += 64) n2 = fma((double)c[m], (double)c[m], n2);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+        if (lane == 0) P.cn2[i] = (float)n2;
+    } else if (tid < 192) {
+        if (P.hm) {   // incremental path (k <= 128): min of row i over each 32-centroid block (h[i][i] = 0)
+            const int j = tid - 64;
+            float m = j < k ? hrow[j] : INFINITY;
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) m = fminf(m, __shfl_xor(m, o));
+            if ((j & 31) == 0) P.hm[4 * i + (j >> 5)] = m;
+        }
+    } else if (lane == 0) {
+        P.s[i] = fminf(fminf(red[0], red[1]), fminf(red[2], red[3]));
+        if (i == 0) P.st->ec_max = fmaxf(fmaxf(redm[0], redm[1]), fmaxf(redm[2], redm[3]));
     }
 }
 
@@ -1196,7 +1213,36 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
     const int j = blockIdx.x, d = P.d, k = P.k;
     // The exact sums of the step: the reduced row, or on the incremental
     // path the running sums plus the reduced moves (wrap-around integers).
-    auto total = [&](int64_t o) { return P.sums ? P.sums[o] + P.total[o] : P.total[o]; };
+    // (general incremental path: the running sums plus the accumulation rows).
+    auto total = [&](int64_t o) {
+        if (P.rows) {
+            uint64_t v = P.sums[o];
+#pragma unroll
+            for (int r = 0; r < kGenRows; ++r) v += P.rows[(int64_t)r * P.L + o];
+            return v;
+        }
+        return P.sums ? P.sums[o] + P.total[o] : P.total[o];
+    };
+    auto clear = [&](int64_t o) {
+        if (P.rows) {
+#pragma unroll
+            for (int r = 0; r < kGenRows; ++r) P.rows[(int64_t)r * P.L + o] = 0;
+        } else {
+            P.total[o] = 0;
+        }
+    };
+    // Everything the wave reads first is requested at once (the sums of its
+    // first 64 dimensions, its count, for cluster 0 the counters): one trip to
+    // memory instead of three.
+    const int64_t o0 = (int64_t)j * d + min((int)threadIdx.x, d - 1);
+    const uint64_t tv0 = total(o0);
+    const double cold0 = P.C64[o0];
+    uint64_t tot[kNumStat];   // the step's counters over the accumulation rows (a lane per row)
+    if (j == 0 && P.rows) {
+#pragma unroll
+        for (int c = 0; c < kNumStat; ++c)
+            tot[c] = P.rows[(int64_t)min((int)threadIdx.x, kGenRows - 1) * P.L + (int64_t)k * d + k + c];
+    }
     const uint64_t count = total((int64_t)k * d + j);
     auto mean = [&](uint64_t v) {
         const int64_t q = (int64_t)(v - count * kMagicBits);
@@ -1220,11 +1266,11 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
     double dr = 0.0, de = 0.0;
     for (int m = threadIdx.x; m < d; m += 64) {
         const int64_t o = (int64_t)j * d + m;
-        const double cold = P.C64[o];
-        const uint64_t tv = total(o);
+        const double cold = m < 64 ? cold0 : P.C64[o];
+        const uint64_t tv = m < 64 ? tv0 : total(o);
         const double cnew = keep ? cold : mean(tv) / scale;
         if (P.sums) P.sums[o] = tv;
-        P.total[o] = 0;
+        clear(o);
         const double df = cnew - cold;
         dr = fma(df, df, dr);
         const float c32 = (float)cnew;
@@ -1242,7 +1288,7 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
         P.f[j] = f32_up(sqrt(dr) * (1.0 + 0x1p-40));
         P.ec[j] = f32_up(sqrt(de) * (1.0 + 0x1p-40));
         if (P.sums) P.sums[(int64_t)k * d + j] = count;
-        P.total[(int64_t)k * d + j] = 0;
+        clear((int64_t)k * d + j);
         if (P.dhi) {   // cumulative drift, bracketed (Elkan lower bounds, incremental bounds)
             const double fd = sqrt(dr);
             const double hi = (P.dhi[j] + fd * (1.0 + 0x1p-40)) * (1.0 + 0x1p-50);
@@ -1253,8 +1299,16 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
             if (P.ddnf) P.ddnf[j] = f32_down(lo);
         }
     }
+    if (j == 0 && P.rows) {
+#pragma unroll
+        for (int c = 0; c < kNumStat; ++c) {
+            const bool row = (int)threadIdx.x < kGenRows;
+            if (row) P.rows[(int64_t)threadIdx.x * P.L + (int64_t)k * d + k + c] = 0;
+            tot[c] = wave_sum_u64(row ? tot[c] : 0);
+        }
+    }
     if (j == 0 && threadIdx.x == 0) {
-        uint64_t* sc = P.total + (int64_t)k * d + k;
+        uint64_t* sc = P.rows ? tot : P.total + (int64_t)k * d + k;
         const int64_t changed = (int64_t)sc[kStChanged];
         const int64_t computed = (int64_t)sc[kStComputed];
         const int64_t c1 = (int64_t)sc[kStClause1];

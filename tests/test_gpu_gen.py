@@ -1,0 +1,98 @@
+"""The general incremental steps (any d; one lane per survivor on "lds-vector",
+matrix cores on "lds-inc") on the GPU.
+
+KM_FLAG_FULL_SUMS takes the same problem through the general assignment kernel
+(every row read and summed each step), which is pinned to the oracle: both
+must give the same bits.  The sizes sit at the edges of the kernels' tiles:
+16-dimension k-steps and their remainders, rows of 4-byte and of 16-byte
+alignment, the 32-centroid blocks, 64-point sub-steps, the rule between the
+two forms (k times d rounded up to 4, at most 256) and the largest k.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from parity import check_assign, check_centroids
+
+import paper_1902_09527_amd as km
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _gpu(a):
+    return torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(DEV)
+
+
+def _same(Xg, Cg, iters, **kw):
+    a1, c1, s1 = km.run(Xg, Cg, iters, **kw)
+    a2, c2, s2 = km.run(Xg, Cg, iters, full_sums=True, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(a1, a2) and torch.equal(c1.view(torch.int32), c2.view(torch.int32))
+    assert s1["iterations"] == s2["iterations"] and s1["changed_last"] == s2["changed_last"]
+    return a1, c1, s1
+
+
+CASES = [
+    # n, d, k, path
+    (1000, 1, 5, "lds-vector"), (63, 3, 7, "lds-vector"), (64 * 5 + 1, 4, 64, "lds-vector"),
+    (3000, 4, 65, "lds-inc"), (5000, 8, 32, "lds-vector"), (5000, 8, 33, "lds-inc"),
+    (2000, 12, 21, "lds-vector"), (2001, 12, 22, "lds-inc"), (700, 10, 1, "lds-vector"),
+    (4097, 15, 32, "lds-inc"), (4096, 17, 33, "lds-inc"), (300000 + 7, 20, 64, "lds-inc"),
+    (3001, 31, 65, "lds-inc"), (3000, 33, 100, "lds-inc"), (6000, 48, 128, "lds-inc"),
+    (2500, 63, 30, "lds-inc"), (2500, 64, 31, "lds-inc"), (2500, 65, 40, "lds-inc"),
+    (4000, 5, 129, "lds-inc"), (4001, 9, 256, "lds-inc"), (3000, 5, 257, "lds-vector"),
+    (1500, 129, 33, "lds-inc"), (1201, 255, 20, "lds-inc"), (900, 600, 9, "lds-inc"),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "n%d-d%d-k%d" % c[:3])
+@pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "offset4"])
+def test_general_step_matches_the_full_read_path(case, offset):
+    n, d, k, path = case
+    print("case", case, offset, flush=True)
+    X, C0 = synth.blobs(n, d, k, seed=700 + n % 97 + d, spread=4.0, sigma=1.5, comps=max(1, k // 2))
+    Cg = _gpu(C0)
+    big = torch.zeros(n * d + offset, dtype=torch.float32, device=DEV)
+    big[offset:] = _gpu(X).reshape(-1)
+    Xg = big[offset:].view(n, d)     # rows at a 4-byte offset from 16-byte alignment with offset = 1
+    with km.KMeansMTI(Xg, Cg) as ctx:
+        assert ctx.path() == path
+    a, c, st = _same(Xg, Cg, 12)
+    if n < 10000:
+        ref = oracle.lloyd(X, C0, 12)
+        assert st["iterations"] == ref["iters"]
+        check_assign(a.cpu().numpy(), ref["assign"], ref["best"], ref["second"])
+        check_centroids(c.cpu().numpy(), ref["C"], X)
+
+
+@pytest.mark.parametrize("d,k", [(7, 9), (24, 40), (70, 20)])
+def test_general_step_out_of_range_rows_ties_and_spherical(d, k):
+    X, C0 = synth.blobs(3000, d, k, seed=811 + d, spread=4.0, sigma=1.5)
+    C0[1] = C0[0]                              # exact ties: the lower index wins every point
+    X[500:700] = X[0]                          # duplicate rows
+    Cg = _gpu(C0)
+    _same(_gpu(X), Cg, 10)
+    a, _, _ = km.run(_gpu(X), Cg, 1)
+    assert not (a == 1).any()
+    Xb = X.copy()
+    Xb[1234] *= 1e6                            # far outside the sample's bound (f16 overflows: direct form)
+    Xb[17] *= 1e-12
+    _same(_gpu(Xb), Cg, 10)
+    Cb = C0.copy()
+    Cb[2] += 1e7                               # a centroid far outside the data keeps its place, empty
+    _, c, _ = _same(_gpu(X), _gpu(Cb), 10)
+    assert torch.equal(c[2], _gpu(Cb)[2])
+    _same(_gpu(X), _gpu(np.abs(C0) + 0.1), 10, spherical=True)
+    for scale in (1e-15, 1e15):                # the scaling of the f16 operands follows the data
+        _same(_gpu(X * np.float32(scale)), _gpu(C0 * np.float32(scale)), 6)
+
+
+def test_general_step_with_infinite_and_nan_rows_ends():
+    X, C0 = synth.blobs(2000, 20, 12, seed=821, spread=4.0, sigma=1.5)
+    X[5, 3] = np.inf
+    X[9, 0] = np.nan
+    a, _, st = km.run(_gpu(X), _gpu(C0), 5)
+    assert st["iterations"] == 5 and int(a.min()) >= 0 and int(a.max()) < 12
