@@ -380,6 +380,27 @@ int read_state(km_ctx* c, km::IterState* out) {
     return KM_OK;
 }
 
+// Whether a problem whose centroids would fit in LDS goes to the global path:
+// from k = 257 on, where only the general kernel (every row read, one scalar
+// scan per survivor) is left beside it.  Per step, general kernel and global
+// path: 1M x 10, k = 477 4.82 and 0.33 ms; 157K x 4, k = 593 0.32 and 0.14 ms;
+// 5000 x 6, k = 900 0.39 and 0.07 ms.  The path keeps split rows and candidate
+// lists (64 bytes per 16 dimensions and per 256 centroids, and about 60 more, a
+// row), the general kernel 8 bytes a row: where that is much memory it has to
+// be there twice over.
+bool large_pays(int64_t n, int32_t d, int32_t k) {
+    if (k <= km::kGenMatMaxK || d > km::kLgMaxD || k >= 0xffff) return false;
+    const double need = (double)n * (64.0 * km::split_chunks(d) + 64.0 * ((k + km::kLgN - 1) / km::kLgN) + 60.0);
+    if (n > INT_MAX || need > 64.0 * (1 << 30)) return false;
+    if (need < 1.0 * (1 << 30)) return true;
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return 2.0 * need <= (double)avail;
+}
+
 // Set-up of a context.  max_iters / tol_n: the stop rule written into the
 // loop state; sync: wait for the set-up work before returning.
 int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const float* C0, int32_t max_iters,
@@ -509,6 +530,11 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
         if (want < cus) want = nwt < cus ? nwt : cus;
         c->gg = (int)(G < want ? G : want);
         v.G = 1;
+    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY | KM_FLAG_STATS |
+                                         KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE)) &&
+               large_pays(n, d, k)) {
+        // More centroids than the incremental steps take: the global path,
+        // although the general kernel's tables would fit in LDS.
     } else if (!(c->flags & KM_FLAG_LARGE_PATH)) {
         c->variant = km::assign_variant(d, k, aligned, (c->flags & KM_FLAG_VECTOR_ONLY) != 0, elkan);
         const bool h_lds = km::assign_h_lds(c->variant % 16, k);
@@ -577,7 +603,7 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
             (rc2 = c->alloc(&L.mv, (size_t)L.mvcap)) || (rc2 = c->alloc(&v.sums, (size_t)k * d + k)) ||
             (rc2 = c->alloc(&L.cs, (size_t)L.nct * km::kLgN * L.nch * 16)) ||
             (rc2 = c->alloc(&L.cn2p, (size_t)L.nct * km::kLgN)) || (rc2 = c->alloc(&L.smin, (size_t)km::kLgTableSplit * k)) ||
-            (rc2 = c->alloc(&L.cand, (size_t)n * L.nct * 8)))
+            (rc2 = c->alloc(&L.cand, (size_t)n * L.nct * 16)))
             return rc2;
         zr.add(L.nsurv, 4 * sizeof(uint32_t));
         zr.add(L.nfull, 4 * sizeof(uint32_t));

@@ -118,6 +118,7 @@ struct FullPart {
     double D;
     int32_t j, rk;
 };
+constexpr int kMultiCand = 6;        // candidates kept with a survivor (16 bits each; k < 65535)
 constexpr int kFullCap = 4096;       // survivors per step whose decision is split over blocks
 constexpr int kFullSplit = 8;        // blocks (centroid ranges) per split decision
 
@@ -138,7 +139,7 @@ struct Large {
     uint32_t* nfull;      // their count
     FullPart* fpart;      // kFullCap x kFullSplit: the ranges' bests of the split decisions
     uint32_t* fcnt;       // kFullCap: ranges done per split survivor (reset by the combining block)
-    int4* mq;             // n: survivors with 2-3 candidates (list entry, candidates, -1 for none)
+    int4* mq;             // n: survivors with 2-6 candidates (list entry, then 16 bits each, 0xffff for none)
     uint32_t* nmq;        // their count
     int4* mv;             // mvcap moves of the step: point, old cluster, new cluster
     uint32_t* nmv;        // their count (nsurv, nfull, nmq, nmv: zeroed by the centroid-table pass)
@@ -146,8 +147,8 @@ struct Large {
     uint32_t* cs;         // nct * kLgN split rows of the float32 centroids (rows >= k zero)
     float* cn2p;          // nct * kLgN: their float32 squared norms (rows >= k: +inf)
     float* smin;          // kLgTableSplit x k: column minima of the half-distance table (reduced to s)
-    uint2* cand;          // n x nct x 2 x 4: per survivor, centroid tile and half of it, the four
-                          // smallest expanded distances (float bits) with their centroids
+    uint32_t* cand;       // n x nct x 4 x 4: per survivor, centroid tile and quarter of it (half tile, half-wave), the
+                          // four smallest expanded distances as ascending keys (float bits, the low 8 the place)
     int32_t nch;          // chunks per split row
     int32_t nct;          // centroid tiles
     int32_t Gs;           // blocks of the histogram / scatter passes

@@ -12,9 +12,9 @@
 //   k_refine_large      per survivor, the candidates within the expanded
 //                       form's error bound; a lone candidate settles it;
 //   k_multi_large,
-//   k_full_large        two or three candidates: direct form and the
-//                       float64 near-tie rule; four or more: float64 over
-//                       all centroids;
+//   k_full_large        two to kMultiCand candidates: direct form and the
+//                       float64 near-tie rule; more: float64 over all
+//                       centroids;
 //   k_hist_large        per-block cluster counts of the new assignment;
 //   k_scan_large_cols,
 //   k_scan_large_clusters  cluster starts and per-block write offsets;
@@ -43,25 +43,6 @@ namespace {
 constexpr int kTiTile = 16;   // centroid rows per block of the tiled centroid table
 constexpr int kTiSplit = kLgTableSplit;
 constexpr int kRefineFlush = 128;   // LDS entries of the refinement pass that trigger a flush
-
-// Insert (v, j) into an ascending 4-list ordered by value, then index.
-__device__ inline void top4_insert(float (&L)[4], int (&J)[4], float v, int j) {
-    if (!(v < L[3] || (v == L[3] && j < J[3]))) return;
-    L[3] = v;
-    J[3] = j;
-#pragma unroll
-    for (int q = 3; q > 0; --q) {
-        const bool sw = L[q] < L[q - 1] || (L[q] == L[q - 1] && J[q] < J[q - 1]);
-        if (sw) {
-            const float tv = L[q];
-            L[q] = L[q - 1];
-            L[q - 1] = tv;
-            const int tj = J[q];
-            J[q] = J[q - 1];
-            J[q - 1] = tj;
-        }
-    }
-}
 
 // Adds each of n counters (summed over the block) to its slot of the step's
 // statistics, one atomic per counter and block (per-wave atomics on the same
@@ -249,9 +230,8 @@ __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ sr
 // low 8 bits (6 within a lane's list) replaced by the centroid's place in
 // the item, which lowers the value by less than 2^-15 of itself.  A lane
 // keeps, per survivor column, the four smallest keys by min and med3
-// (branch-free); the two half-waves' lists of a column are merged by a lane
-// swap, and each wave writes the four smallest (value, centroid) pairs of
-// its 128 centroids to the candidate buffer.
+// (branch-free), and writes the four, with the centroid's place in the item,
+// to the candidate buffer.
 
 __device__ __forceinline__ int lg_swz(int rho) { return ((rho >> 2) & 3) ^ (((rho >> 1) & 1) << 1); }
 
@@ -492,29 +472,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             }
             sort4(KP[cb]);
         }
-        // Half-wave h keeps column 32 h + col and merges in the other half's
-        // list of it (a lane swap; no LDS store may follow the ring's loads
-        // without waiting for them).
-        uint32_t mine[4], other[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            mine[q] = half ? KP[1][q] : KP[0][q];
-            other[q] = __shfl_xor(half ? KP[0][q] : KP[1][q], 32);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) key4_insert(mine, other[q]);
+        // Both half-waves' lists of a column go out: four keys for each 64
+        // centroids (merged to four for 128 they overflowed where several
+        // centroids share a component; the keys alone are half the words of
+        // (value, centroid) pairs).
         const int rows = min(kLgM, ns - cs0);
-        const int sc = 64 * wc + 32 * half + col;
-        if (sc < rows) {
-            uint32_t o[8];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                o[2 * q] = mine[q] & ~255u;
-                o[2 * q + 1] = (uint32_t)cn0 + (mine[q] & 255u);
-            }
-            uint4* dst = reinterpret_cast<uint4*>(Lg.cand + (((int64_t)(cs0 + sc) * nct + cn0 / kLgN) * 2 + wr) * 4);
-            dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
-            dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
+        for (int cb = 0; cb < 2; ++cb) {
+            const int sc = 64 * wc + 32 * cb + col;
+            if (sc < rows)
+                reinterpret_cast<uint4*>(Lg.cand)[(((int64_t)(cs0 + sc) * nct + cn0 / kLgN) * 2 + wr) * 2 + half] =
+                    make_uint4(KP[cb][0], KP[cb][1], KP[cb][2], KP[cb][3]);
         }
         // Next item of the compute cursor.
         cc = 0;
@@ -531,18 +499,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 // ---------------------------------------------------------------------------
-// Refinement of every survivor by a thread pair (each merging half of its
-// candidate lists: four per centroid tile and half of it): only centroids
-// within twice the expanded form's error bound of the smallest can be the
+// Refinement of every survivor by a thread pair (each reading half of its
+// candidate lists: the four smallest keys of each 64 centroids): only
+// centroids within twice the expanded form's error bound of the smallest can be the
 // nearest.  A lone candidate is the assignment, its bound taken from the
-// expanded value; two or three go to k_multi_large (direct form, float64
-// near-tie rule); a survivor whose four smallest all lie inside the bound
-// (more may lie outside the lists) goes to k_full_large, which decides it in
-// float64 over all centroids.
+// expanded value; two to kMultiCand go to k_multi_large (direct form, float64
+// near-tie rule); a survivor with more, or with four from one list (more
+// of its 64 centroids may lie outside it), goes to k_full_large, which decides it in
+// float64 over all centroids: 2 MB of centroids read per survivor at k = 1000,
+// d = 256, so that it has to stay rare.  Where several centroids share a
+// component (uneven weights, start rows drawn from the data) four to six
+// candidates are common; sent to the full decision they made a step of 700K x
+// 128, k = 56 take 1.5 ms and one of 2M x 256, k = 1000 with Dirichlet weights
+// 154 ms (now 24 ms), one of 400K x 128, k = 200 3.5 ms (now 0.35 ms).
 //
-// Error bound of an expanded value (x and c the float32 row and centroid):
-//   - |x|^2, |c|^2, the float32 roundings: (d + 8) 2^-24 R^2 with
-//     R = |x| + max |c| (the float32 model of the other paths);
+// Error bounds (x and c the float32 row and centroid).  What decides between
+// centroids is |c|^2 - 2 x.c (a row's own norm shifts all of them alike):
 //   - the split product: dropping lo.lo and the residuals of the two
 //     roundings costs at most 3.04 2^-16 |x_m| |c_m| per dimension;
 //   - the bf16 products are exact in float32 and each instruction adds 16
@@ -552,11 +524,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 //     17 addends to the largest), the 3 ceil(d/16) instructions of a
 //     product contribute at most 6.9 d' 2^-24 sum_m |x_m| |c_m|, d' = 16
 //     ceil(d / 16);
-//   - the packed key lowers a value by less than 2^-15 of itself (<= R^2);
-//   so a value is within gexp R^2 + 2 (778 + 6.9 d') 2^-24 |x| max |c| +
-//   2^-15 R^2 of the distance, plus an absolute 2^-100 (1 + R) for bf16
-//   values below the normal range.  Rows with |x|^2 or R out of range
-//   (non-finite data) are decided in float64 over all centroids.
+//   - |c|^2 summed in float32: (d / 64 + 16) 2^-24 |c|^2 (lanes share the
+//     dimensions), at most (d + 8) 2^-24 |c|^2; two additions and the norm's
+//     rounding at the magnitude of the values: 4 2^-24 R^2, R = |x| + max |c|;
+//   so a value is within e = (d + 8) 2^-24 max |c|^2 + 4 2^-24 R^2 +
+//   2 (778 + 6.9 d') 2^-24 |x| max |c| of the row's common offset, plus an
+//   absolute 2^-100 (1 + R) for bf16 values below the normal range.
+// The packed key lowers a value v by less than 2^-15 of itself: the key of
+// every centroid that can be nearest is at most (T0 (1 + 2^-15) + 2 e), T0 the
+// smallest key, itself lowered (T0 is a squared distance, far below R^2 where
+// rows are near their centroid; with 2^-15 R^2 instead, 700K x 128, k = 56 sent
+// so many survivors to the full decision that it took 1 ms a step).  The
+// bound of a lone candidate adds the row's norm, (d + 8) 2^-24 |x|^2.  Rows with
+// |x|^2 or R out of range (non-finite data) are decided in float64 over all
+// centroids.
 
 __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
     IterState* st = P.st;
@@ -577,10 +558,18 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
     __syncthreads();
     const float cnmax = sqrtf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))) * kUp;
     const float ecm = st->ec_max;
-    const float gexp = (float)(d + 8) * 0x1p-24f + 0x1p-15f;
+    const float gexp = (float)(d + 8) * 0x1p-24f;
     const float gsp2 = 2.f * (778.f + 6.9f * (float)(16 * Lg.nch)) * 0x1p-24f * (1.f + 0x1p-10f);
     uint64_t my_changed = 0, my_comp = 0, my_rc = 0;
-    const int part = tid & 1;
+    // A group of lps lanes (a power of two, 2 nct or more up to 64) shares a
+    // survivor, a lane per two candidate lists: one coalesced read of its
+    // keys.
+    int lps = 4;
+    while (lps < 2 * nct && lps < 64) lps *= 2;
+    const int np = 2 * nct;   // pairs of lists
+    const int gl = tid & (lps - 1), per = 256 / lps;
+    const uint64_t gmask = (lps == 64 ? ~0ull : (1ull << lps) - 1ull) << (lane & ~(lps - 1));
+    const uint64_t below = gmask & ((1ull << lane) - 1ull);
     // Queued survivors and moves gather in LDS and go to the global lists
     // with one atomic per flush of up to 2 kRefineFlush entries (a global
     // counter per wave would take one atomic per 64 survivors).
@@ -614,87 +603,147 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
     };
 
     const bool rec_moves = !first && !(P.flags & KM_FLAG_STATS);
-    for (int64_t c0 = (int64_t)blockIdx.x * 128; c0 < (int64_t)ns; c0 += (int64_t)gridDim.x * 128) {
-        const int64_t c = c0 + (tid >> 1);
-        int4 mvr = make_int4(0, 0, 0, 0), mqr = make_int4(0, 0, 0, 0);
-        bool moved = false, queued = false;
-        if (c < (int64_t)ns) {   // both threads of a pair
-        float T[4];
-        int TJ[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            T[q] = INFINITY;
-            TJ[q] = INT_MAX;
-        }
-        // The pair reads half of the 8 nct candidates each, then each merges
-        // in the other's four: the same list in both (a total order).
-        const uint4* cl = reinterpret_cast<const uint4*>(Lg.cand + c * nct * 8) + part * 2 * nct;
-        for (int q = 0; q < 2 * nct; ++q) {
-            const uint4 v = cl[q];
-            top4_insert(T, TJ, __uint_as_float(v.x), (int)v.y);
-            top4_insert(T, TJ, __uint_as_float(v.z), (int)v.w);
-        }
-        {
-            float OT[4];
-            int OJ[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                OT[q] = __shfl_xor(T[q], 1);
-                OJ[q] = __shfl_xor(TJ[q], 1);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) top4_insert(T, TJ, OT[q], OJ[q]);
-        }
-        const int64_t i = Lg.surv[c];
-        const int inc = first ? -1 : P.a[i];
-        const float x2 = Lg.sx2[c];
+    // A block takes runs of kRefineFlush list entries (rpf rounds), neighbours
+    // in the list being neighbours in the point arrays.  A round's loads are
+    // requested a round ahead (two ahead took as long); the buffers are looked
+    // at (behind barriers) once per run, which appends at most kRefineFlush
+    // entries.
+    struct Next {
+        uint4 v[2];
+        int64_t i;
+        float x2;
+        int inc;
+    } nx;
+    // Lists 2 l and 2 l + 1 of a survivor (none past its np pairs).
+    auto pair_at = [&](const uint4* cl, int l, uint4 (&v)[2]) __attribute__((always_inline)) {
+        const uint4 none = make_uint4(~0u, ~0u, ~0u, ~0u);
+        v[0] = l < np ? cl[2 * l] : none;
+        v[1] = l < np ? cl[2 * l + 1] : none;
+    };
+    const int rpf = kRefineFlush / per;
+    auto entry = [&](int64_t c0) __attribute__((always_inline)) { return min(c0 + tid / lps, (int64_t)ns - 1); };
+    int32_t i2 = 0;   // the point of the round after the next
+    auto fetch = [&](int64_t c0) __attribute__((always_inline)) {
+        const int64_t cc = entry(c0);
+        // the survivor's 4 nct lists (ascending keys; list l covers half
+        // (l / 2) % 2 of centroid tile l / 4)
+        pair_at(reinterpret_cast<const uint4*>(Lg.cand) + cc * nct * 4, gl, nx.v);
+        nx.i = i2;
+        nx.x2 = Lg.sx2[cc];
+        nx.inc = first ? -1 : P.a[i2];
+    };
+    // First entry of this block's round r.
+    auto start_of = [&](int64_t r) __attribute__((always_inline)) {
+        return ((int64_t)blockIdx.x + r / rpf * gridDim.x) * kRefineFlush + r % rpf * per;
+    };
+    int64_t round = 0;
+    if (start_of(0) < (int64_t)ns) {
+        i2 = Lg.surv[entry(start_of(0))];
+        fetch(start_of(0));
+        i2 = Lg.surv[entry(start_of(1))];
+    }
+    for (int64_t c0 = start_of(0); start_of(round / rpf * rpf) < (int64_t)ns; c0 = start_of(++round)) {
+        const int64_t c = c0 + tid / lps;
+        const bool live = c < (int64_t)ns, lead = live && gl == 0;
+        const uint4* cl = reinterpret_cast<const uint4*>(Lg.cand) + (live ? c : (int64_t)ns - 1) * nct * 4;
+        uint4 v[2] = {nx.v[0], nx.v[1]};
+        const int64_t i = nx.i;
+        const float x2 = nx.x2;
+        const int inc = nx.inc;
+        fetch(start_of(round + 1));
+        i2 = Lg.surv[entry(start_of(round + 2))];
+        // The smallest key of all.
+        uint32_t k0 = min(v[0].x, v[1].x);
+        for (int l = gl + 64; l < np; l += 64) k0 = min(k0, min(cl[2 * l].x, cl[2 * l + 1].x));   // k > 8192
+        for (int o = 1; o < lps; o <<= 1) k0 = min(k0, __shfl_xor(k0, o));
+        const float T0 = __uint_as_float(k0 & ~255u);
         const float xn = sqrtf(fmaxf(x2, 0.f)) * kUp;
         const float R = xn + cnmax;
-        const float e1 = gexp * R * R + gsp2 * xn * cnmax + 4.f * R * ecm + 2.f * ecm * ecm + 0x1p-100f * (1.f + R);
-        const float thr = T[0] + 2.f * e1;
+        const float e1 = (gexp * cnmax * cnmax + 0x1p-22f * R * R + gsp2 * xn * cnmax + 4.f * R * ecm +
+                          2.f * ecm * ecm + 0x1p-100f * (1.f + R)) * kUp;
+        const float thr = (T0 * (1.f + 0x1.1p-15f) + 2.f * e1) * kUp;
         // Only centroids whose expanded distance lies within thr of the
         // smallest can be the nearest: any other one is certified farther
-        // than the smallest's centroid.
-        const bool full = T[3] <= thr || !(x2 <= 0x1p120f) || !(R <= 0x1p60f);
-        if (full) {
-            if (part == 0) {
-                Lg.fq[atomicAdd(Lg.nfull, 1u)] = (int32_t)c;
-                my_comp += (uint64_t)k;
-                my_rc += 1;
-            }
-        } else {
+        // than the smallest's centroid.  A list whose four keys all lie
+        // within thr may have left more out.
+        const bool wild = !(x2 <= 0x1p120f) || !(R <= 0x1p60f);
+        const uint32_t kthr = __float_as_uint(thr);   // thr >= 0: keys order as values
+        auto within = [&](uint32_t key) __attribute__((always_inline)) { return (key & ~255u) <= kthr; };
         int nq = 0;
-        while (nq < 3 && T[nq] <= thr && TJ[nq] < k) ++nq;   // uniform in the pair
+        bool cut = false;
+        auto count = [&](const uint4 (&u)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint64_t last = __ballot(within(u[h].w)) & gmask;
+                nq += __popcll(__ballot(within(u[h].x)) & gmask) + __popcll(__ballot(within(u[h].y)) & gmask) +
+                      __popcll(__ballot(within(u[h].z)) & gmask) + __popcll(last);
+                cut |= last != 0;
+            }
+        };
+        count(v);
+        for (int l = gl + 64; l - gl < np; l += 64) {   // k > 8192
+            uint4 u[2];
+            pair_at(cl, l, u);
+            count(u);
+        }
+        const bool full = wild || cut || nq > kMultiCand || nq == 0;
         // One candidate is the nearest centroid (every other one is certified
         // farther): as on the LDS paths, its bound then comes from its
         // expanded value and the error bound, without the direct form (kept
         // when statistics are gathered).  Otherwise the survivor and its
         // candidates go to k_multi_large.
-        if (nq == 1 && !(P.flags & KM_FLAG_STATS)) {
-            const int b = TJ[0];
-            const float ub = __builtin_amdgcn_sqrtf(fmaxf(T[0] + e1, 0.f)) * (1.0f + 0x1p-20f) * kUp;
-            if (part == 0) {
-                if (b != inc) {
-                    P.a[i] = b;
-                    my_changed += 1;
-                    moved = true;
-                    mvr = make_int4((int)i, inc, b, 0);
-                }
-                P.u[i] = ub;
-                my_comp += (uint64_t)k;
-            }
-        } else if (part == 0) {
-            queued = true;
-            mqr = make_int4((int)c, TJ[0], nq > 1 ? TJ[1] : -1, nq > 2 ? TJ[2] : -1);
-            my_comp += (uint64_t)k;
+        const bool single = !full && nq == 1 && !(P.flags & KM_FLAG_STATS);
+        const bool queued = live && !full && !single;
+        if (lead) my_comp += (uint64_t)k;
+        if (full && lead) {
+            Lg.fq[atomicAdd(Lg.nfull, 1u)] = (int32_t)c;
+            my_rc += 1;
         }
-        }   // not full
-        }   // c < ns
-        // At most 128 entries per round, so a buffer of 2 kRefineFlush holds
-        // a round on top of fewer than kRefineFlush waiting entries.
-        if (queued) qb[atomicAdd(&nqb, 1u)] = mqr;
-        if (moved && rec_moves) mb[atomicAdd(&nmb, 1u)] = mvr;
-        flush(false);
+        int b = -1;
+        if (live && single) {   // from the lane that holds it
+            int at = v[0].x == k0 ? 2 * gl : v[1].x == k0 ? 2 * gl + 1 : -1;
+            for (int l = gl + 64; l < np; l += 64)   // k > 8192
+                at = cl[2 * l].x == k0 ? 2 * l : cl[2 * l + 1].x == k0 ? 2 * l + 1 : at;
+            const uint64_t own = __ballot(at >= 0) & gmask;
+            b = (int)__shfl((uint32_t)(at / 4 * kLgN) + (k0 & 255u), __builtin_ctzll(own));
+        }
+        if (lead && single) {
+            const float ub = __builtin_amdgcn_sqrtf(fmaxf(T0 * (1.f + 0x1.1p-15f) + e1 + gexp * x2, 0.f)) *
+                             (1.0f + 0x1p-20f) * kUp;
+            if (b != inc) {
+                P.a[i] = b;
+                my_changed += 1;
+                if (rec_moves) mb[atomicAdd(&nmb, 1u)] = make_int4((int)i, inc, b, 0);
+            }
+            P.u[i] = ub;
+        }
+        if (queued) {   // the group appends its ids after the leader's entry
+            uint32_t e = 0;
+            if (lead) {
+                e = atomicAdd(&nqb, 1u);
+                qb[e] = make_int4((int)c, -1, -1, -1);
+            }
+            e = __shfl(e, lane & ~(lps - 1));
+            uint16_t* ids = reinterpret_cast<uint16_t*>(qb + e) + 2;
+            int done = 0;
+            auto put = [&](uint32_t key, int list) __attribute__((always_inline)) {
+                const uint64_t hm = __ballot(within(key));
+                if (within(key)) ids[done + __popcll(hm & below)] = (uint16_t)(list / 4 * kLgN + (int)(key & 255u));
+                done += __popcll(hm & gmask);
+            };
+            for (int l = gl; l - gl < np; l += 64) {
+                uint4 u[2] = {v[0], v[1]};
+                if (l != gl) pair_at(cl, l, u);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    put(u[h].x, 2 * l + h);
+                    put(u[h].y, 2 * l + h);
+                    put(u[h].z, 2 * l + h);
+                    put(u[h].w, 2 * l + h);
+                }
+            }
+        }
+        if (round % rpf == rpf - 1) flush(false);
     }
     flush(true);
     {
@@ -706,7 +755,7 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
 }
 
 // ---------------------------------------------------------------------------
-// Survivors with two or three candidates inside the bound, one wave each:
+// Survivors with two to kMultiCand candidates inside the bound, one wave each:
 // the candidates' direct-form float32 distances (lanes over the dimensions,
 // coalesced rows, a fixed butterfly: the float32 error bound holds for any
 // summation order), the nearest with the incumbent winning ties, and when
@@ -727,8 +776,13 @@ __global__ __launch_bounds__(256) void k_multi_large(Dev P, Large Lg) {
     for (uint32_t q = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); q < nq_all;
          q += gridDim.x * (blockDim.x >> 6)) {
         const int4 e = Lg.mq[q];
-        const int js[3] = {e.y, e.z, e.w};
-        const int nq = e.w >= 0 ? 3 : (e.z >= 0 ? 2 : 1);
+        const uint32_t ids[3] = {(uint32_t)e.y, (uint32_t)e.z, (uint32_t)e.w};
+        auto js = [&](int t) __attribute__((always_inline)) {
+            const uint32_t v = t < 2 ? ids[0] : t < 4 ? ids[1] : ids[2];
+            return (int)(t & 1 ? v >> 16 : v & 0xffffu);
+        };
+        int nq = 0;
+        while (nq < kMultiCand && js(nq) != 0xffff) ++nq;   // uniform in the wave
         const int64_t i = Lg.surv[e.x];
         const float* xr = P.X + i * d;
         const int inc = first ? -1 : P.a[i];
@@ -769,7 +823,7 @@ __global__ __launch_bounds__(256) void k_multi_large(Dev P, Large Lg) {
         float d1 = INFINITY, d2 = INFINITY;
         int rk1 = INT_MAX, j1 = 0;
         for (int t = 0; t < nq; ++t) {
-            const int j = js[t];
+            const int j = js(t);
             const float Dd = dist32(j);
             const int rk = j == inc ? -1 : j;
             if (Dd < d1 || (Dd == d1 && rk < rk1)) {
@@ -792,7 +846,7 @@ __global__ __launch_bounds__(256) void k_multi_large(Dev P, Large Lg) {
             double Dbb = INFINITY;
             int bb = -1, kb = INT_MAX;
             for (int t = 0; t < nq; ++t) {
-                const int j = js[t];
+                const int j = js(t);
                 const double Dj = dist64(j);
                 const int rk = j == inc ? -1 : j;
                 if (Dj < Dbb || (Dj == Dbb && rk < kb)) {

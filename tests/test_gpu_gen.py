@@ -43,7 +43,7 @@ CASES = [
     (4097, 15, 32, "lds-inc"), (4096, 17, 33, "lds-inc"), (300000 + 7, 20, 64, "lds-inc"),
     (3001, 31, 65, "lds-inc"), (3000, 33, 100, "lds-inc"), (6000, 48, 128, "lds-inc"),
     (2500, 63, 30, "lds-inc"), (2500, 64, 31, "lds-inc"), (2500, 65, 40, "lds-inc"),
-    (4000, 5, 129, "lds-inc"), (4001, 9, 256, "lds-inc"), (3000, 5, 257, "lds-vector"),
+    (4000, 5, 129, "lds-inc"), (4001, 9, 256, "lds-inc"), (3000, 5, 257, "global-mfma"),
     (1500, 129, 33, "lds-inc"), (1201, 255, 20, "lds-inc"), (900, 600, 9, "lds-inc"),
 ]
 
@@ -88,6 +88,19 @@ def test_general_step_out_of_range_rows_ties_and_spherical(d, k):
     _same(_gpu(X), _gpu(np.abs(C0) + 0.1), 10, spherical=True)
     for scale in (1e-15, 1e15):                # the scaling of the f16 operands follows the data
         _same(_gpu(X * np.float32(scale)), _gpu(C0 * np.float32(scale)), 6)
+
+
+@pytest.mark.parametrize("n,d,k", [(20000, 4, 9000), (6000, 40, 4097), (5000, 64, 200), (3000, 17, 300)])
+def test_global_path_candidate_lists_match_oracle(n, d, k):
+    # few components, so that many centroids share one: several candidates per
+    # survivor and full lists; k past 4096 and 8192 centroids (list rounds)
+    X, C0 = synth.blobs(n, d, k, seed=831 + d, spread=4.0, sigma=1.5, comps=12)
+    for stats in (False, True):
+        a, c, st = km.run(_gpu(X), _gpu(C0), 5, large_path=True, stats=stats)
+        ref = oracle.lloyd(X, C0, 5)
+        assert st["iterations"] == ref["iters"]
+        check_assign(a.cpu().numpy(), ref["assign"], ref["best"], ref["second"])
+        check_centroids(c.cpu().numpy(), ref["C"], X)
 
 
 def test_general_step_with_infinite_and_nan_rows_ends():
