@@ -211,43 +211,70 @@ __global__ void k_set_centroids(const float* __restrict__ C0, double* C64, float
 }
 
 // Spherical k-means (the paper's sk-means application): row i of X projected
-// to the unit sphere, x / |x| with the norm and the quotient in float64
-// (a zero row stays zero).
-__global__ void k_normalize_rows(const float* __restrict__ X, int64_t n, int32_t d, float* __restrict__ Xn) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+// to the unit sphere, x / |x| with the norm and the quotient in float64 (a
+// zero row stays zero).  G lanes share a row (G a power of two, at most 64,
+// about d / 4), so that its loads and stores are coalesced: bound by the read
+// and write of X.  With a thread per row every load of a wave fell on 64
+// lines: 400K x 128 took 2.11 ms, now 0.107 ms (3.8 TB/s).
+template <int G>
+__global__ __launch_bounds__(256) void k_normalize_rows(const float* __restrict__ X, int64_t n, int32_t d,
+                                                        float* __restrict__ Xn) {
+    const int64_t stride = (int64_t)gridDim.x * (256 / G);
+    const int g = threadIdx.x & (G - 1);
+    // whole groups take every round (shuffles); rows past n repeat the last
+    for (int64_t i0 = (int64_t)blockIdx.x * (256 / G); i0 < n; i0 += stride) {
+        const int64_t i = min(i0 + threadIdx.x / G, n - 1);
         const float* x = X + i * d;
+        constexpr int H = 4;   // coordinates held per lane (a wider row is read again)
+        float h[H];
         double s = 0.0;
-        for (int m = 0; m < d; ++m) s = fma((double)x[m], (double)x[m], s);
+#pragma unroll
+        for (int e = 0; e < H; ++e) {
+            const int m = g + e * G;
+            h[e] = m < d ? x[m] : 0.f;
+            s = fma((double)h[e], (double)h[e], s);
+        }
+        for (int m = g + H * G; m < d; m += G) s = fma((double)x[m], (double)x[m], s);
+#pragma unroll
+        for (int o = 1; o < G; o <<= 1) s += __shfl_xor(s, o);
         const double r = sqrt(s);
+        if (i0 + threadIdx.x / G >= n) continue;
         float* o = Xn + i * d;
-        for (int m = 0; m < d; ++m) o[m] = r > 0.0 ? (float)((double)x[m] / r) : 0.f;
+#pragma unroll
+        for (int e = 0; e < H; ++e) {
+            const int m = g + e * G;
+            if (m < d) o[m] = r > 0.0 ? (float)((double)h[e] / r) : 0.f;
+        }
+        for (int m = g + H * G; m < d; m += G) o[m] = r > 0.0 ? (float)((double)x[m] / r) : 0.f;
     }
 }
 
-// Unit centroids from C0 (one thread per row): float64 master, its float32
+// Unit centroids from C0 (one wave per row): float64 master, its float32
 // copy and that copy's rounding error; *zero is set for a zero row.
-__global__ void k_set_centroids_unit(const float* __restrict__ C0, double* C64, float* C32, float* ec, int32_t k,
-                                     int32_t d, int32_t* zero) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= k) return;
+__global__ __launch_bounds__(64) void k_set_centroids_unit(const float* __restrict__ C0, double* C64, float* C32,
+                                                           float* ec, int32_t k, int32_t d, int32_t* zero) {
+    const int j = blockIdx.x, lane = threadIdx.x;
     const float* c = C0 + (int64_t)j * d;
     double s = 0.0;
-    for (int m = 0; m < d; ++m) s = fma((double)c[m], (double)c[m], s);
+    for (int m = lane; m < d; m += 64) s = fma((double)c[m], (double)c[m], s);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
     if (!(s > 0.0)) {
-        atomicOr(zero, 1);
+        if (lane == 0) atomicOr(zero, 1);
         s = 1.0;
     }
     const double r = sqrt(s);
     double e2 = 0.0;
-    for (int m = 0; m < d; ++m) {
+    for (int m = lane; m < d; m += 64) {
         const double v = (double)c[m] / r;
         const float v32 = (float)v;
         C64[(int64_t)j * d + m] = v;
         C32[(int64_t)j * d + m] = v32;
         e2 = fma((double)v32 - v, (double)v32 - v, e2);
     }
-    ec[j] = f32_up(sqrt(e2) * (1.0 + 0x1p-40));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) e2 += __shfl_xor(e2, o);
+    if (lane == 0) ec[j] = f32_up(sqrt(e2) * (1.0 + 0x1p-40));
 }
 
 // ---------------------------------------------------------------------------
@@ -1398,16 +1425,22 @@ hipError_t launch_init_buffers(const ZeroRanges& z, int cus, hipStream_t s) {
 }
 
 hipError_t launch_normalize_rows(const float* X, int64_t n, int32_t d, float* Xn, hipStream_t s) {
-    int64_t blocks = (n + 255) / 256;
+    int g = 1;
+    while (g < 64 && 4 * g < d) g *= 2;
+    int64_t blocks = (n + 256 / g - 1) / (256 / g);
     if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(k_normalize_rows, dim3((unsigned)blocks), dim3(256), 0, s, X, n, d, Xn);
+    const dim3 grid((unsigned)blocks), block(256);
+#define KM_NORM(G_) case G_: hipLaunchKernelGGL(k_normalize_rows<G_>, grid, block, 0, s, X, n, d, Xn); break;
+    switch (g) {
+        KM_NORM(1) KM_NORM(2) KM_NORM(4) KM_NORM(8) KM_NORM(16) KM_NORM(32) KM_NORM(64)
+    }
+#undef KM_NORM
     return hipGetLastError();
 }
 
 hipError_t launch_set_centroids_unit(const float* C0, double* C64, float* C32, float* ec, int32_t k, int32_t d,
                                      int32_t* zero, hipStream_t s) {
-    hipLaunchKernelGGL(k_set_centroids_unit, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, s, C0, C64, C32, ec,
-                       k, d, zero);
+    hipLaunchKernelGGL(k_set_centroids_unit, dim3((unsigned)k), dim3(64), 0, s, C0, C64, C32, ec, k, d, zero);
     return hipGetLastError();
 }
 
