@@ -84,7 +84,7 @@ enum {
                                   survivors' rows are read after the first step (the
                                   streaming path, d = 16 and k <= 16, and the incremental
                                   matrix-core path, d = 16 or 32 and k <= 128); same results.
-                                  Implied by KM_FLAG_STATS. */
+                                  On the streaming path implied by KM_FLAG_STATS. */
     KM_FLAG_SPHERICAL = 256u,  /* spherical k-means (the paper's sk-means application): the
                                   rows of X are projected to the unit sphere (into a copy the
                                   context owns; a zero row stays zero) and C0 likewise, the
@@ -114,7 +114,8 @@ typedef struct {
     int64_t dist_lloyd;        /* n * k * iterations: what unpruned Lloyd's evaluates */
     int64_t clause1_skips;     /* point-iterations skipped whole by Clause 1 */
     int64_t rechecks;          /* points decided again in float64 (near ties) */
-    double inertia_last;       /* last step's inertia (float32 distances summed exactly); NaN without KM_FLAG_STATS */
+    double inertia_last;       /* last step's inertia (where every row is read float32 distances summed exactly, else
+                                  from the exact per-cluster sums and the sum of |x|^2); NaN without KM_FLAG_STATS */
     double device_ms;          /* run only: device time of the iteration loop (HIP events); else 0 */
 } km_stats;
 
@@ -204,9 +205,11 @@ int kmeans_mti_run(const float* X, int64_t n, int32_t d, int32_t k, const float*
  * read, the survivors are settled on the matrix cores and the moves of the
  * points whose cluster changed are summed: k_inc_mm for d = 16 or 32 and k <=
  * 128, then k_reduce, k_update, k_centroid_table; k_inc_mat for other d and k
- * <= 256 while its tables fit in LDS, then k_update, k_centroid_table),
+ * <= 256 while its tables fit in LDS, then k_update, k_centroid_table; with
+ * KM_FLAG_STATS k_inc_mat also takes d = 16 or 32, reported as "lds-mfma" for
+ * 16 < k <= 128),
  * "lds-elkan" (the
- * same with KM_FLAG_ELKAN's lower-bound scan), "global-mfma"
+ * general kernel with KM_FLAG_ELKAN's lower-bound scan), "global-mfma"
  * (centroids or sums too large for LDS: dense MFMA survivors, sums by
  * counting sort).  "" for a NULL context.
  */
@@ -296,8 +299,8 @@ int kmeans_pp_seed_noalloc(const float* X, int64_t n, int32_t d, int32_t k, cons
  * For each run q = 0..r-1: seed k rows with kmeans_pp_seed from the uniforms
  * U[q*k .. q*k + k - 1], run k-means from those seeds as kmeans_mti_run does
  * (max_iters, tol, flags with KM_FLAG_STATS added), and keep the run with the
- * least final inertia (float32 distances summed exactly); an exact tie keeps
- * the earlier run.
+ * least final inertia (km_stats.inertia_last); an exact tie keeps the earlier
+ * run.
  *
  * X: device, n x d float32.  U: HOST, r * k doubles in [0, 1).  assign_out
  * (n int32) and C_out (k x d float32): device, receive the kept run's

@@ -493,8 +493,8 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
             if (gi > want) gi = want > 0 ? want : 1;
             c->gi = (int)gi;
         }
-    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY | KM_FLAG_STATS |
-                                         KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE)) &&
+    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY |
+                                         KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE | KM_FLAG_STATS)) &&
                km::inc_mm_applies(n, d, k, aligned) && km::inc_mm_lds(d, km::inc_mm_kb(k)).bytes <= max_lds) {
         // Incremental matrix-core step: only the Clause-1 survivors' rows are read.
         c->incmm = true;
@@ -510,7 +510,7 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
         if (G > want) G = want > 0 ? want : 1;
         c->gim = (int)G;
         v.G = (int32_t)G;
-    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY | KM_FLAG_STATS |
+    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY |
                                          KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE)) &&
                (c->gen = km::gen_kind(n, d, k, max_lds)) != km::kGenNone) {
         // General incremental step: resident blocks, at most one wave tile
@@ -530,7 +530,7 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
         if (want < cus) want = nwt < cus ? nwt : cus;
         c->gg = (int)(G < want ? G : want);
         v.G = 1;
-    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY | KM_FLAG_STATS |
+    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY |
                                          KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE)) &&
                large_pays(n, d, k)) {
         // More centroids than the incremental steps take: the global path,
@@ -594,7 +594,6 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
             (rc2 = c->alloc(&L.cnt, (size_t)L.Gs * k)) || (rc2 = c->alloc(&L.off, (size_t)L.Gs * k)) ||
             (rc2 = c->alloc(&L.base, (size_t)k + 1)) || (rc2 = c->alloc(&L.cbase, (size_t)k + 1)) ||
             (rc2 = c->alloc(&L.perm, (size_t)n)) || (rc2 = c->alloc(&L.cpart, (size_t)L.NCmax * d)) ||
-            (rc2 = c->alloc(&L.ciq, (size_t)L.NCmax)) ||
             (rc2 = c->alloc(&L.xs, (size_t)n * L.nch * 16)) || (rc2 = c->alloc(&L.x2, (size_t)n)) ||
             (rc2 = c->alloc(&L.sx2, (size_t)n)) || (rc2 = c->alloc(&L.fq, (size_t)n)) ||
             (rc2 = c->alloc(&L.nfull, 4)) || (rc2 = c->alloc(&L.nmv, 4)) || (rc2 = c->alloc(&L.nmq, 4)) ||
@@ -689,6 +688,18 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
     }
     uint32_t* scratch = nullptr;
     if ((rc = c->alloc(&scratch, 8))) return rc;
+    // Inertia (the kernels that read every row sum their own): the squares of
+    // X are summed with the magnitude scan, the clusters' terms come from the
+    // exact sums of each step, so that no further row has to be read for it.
+    double *x2part = nullptr, *x2sum = nullptr;
+    int nx2 = 0;
+    if ((c->flags & KM_FLAG_STATS) && (c->gen || c->large)) {
+        nx2 = km::absmax_blocks(n * d, cus);
+        if ((rc = c->alloc(&x2part, (size_t)2 * nx2)) || (rc = c->alloc(&x2sum, 2)) ||
+            (rc = c->alloc(&v.iterm, (size_t)2 * k)))
+            return rc;
+        v.x2sum = x2sum;
+    }
     zr.add(scratch, 8 * sizeof(uint32_t));
     zr.add(v.total, sizeof(uint64_t) * (size_t)v.L);
     zr.add(v.rec, sizeof(km::IterRec) * km::kHistCap);
@@ -708,7 +719,8 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
     // kernel's launch).
     c->fuse_scan = c->gf && n * d >= km::kFuseScanMin && !(c->flags & (KM_FLAG_VALIDATE | KM_FLAG_SPHERICAL));
     if (c->small) c->fz.amax = c->fuse_scan ? scratch : nullptr;
-    KM_HIP(km::launch_absmax(X, c->fuse_scan ? 0 : n * d, C0, (int64_t)k * d, X, n, d, cus, scratch, c->stream));
+    KM_HIP(km::launch_absmax(X, c->fuse_scan ? 0 : n * d, C0, (int64_t)k * d, X, n, d, cus, scratch, x2part,
+                             c->stream));
     if (c->flags & KM_FLAG_SPHERICAL)
         KM_HIP(km::launch_set_centroids_unit(C0, v.C64, v.C32, v.ec, k, d, reinterpret_cast<int32_t*>(scratch + 4),
                                              c->stream));
@@ -716,7 +728,8 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
     // host does not wait for them).  Only the checks that decide the call's
     // status read the set-up back: non-finite input (KM_FLAG_VALIDATE) and a
     // zero C0 row (spherical k-means).
-    KM_HIP(km::launch_set_scales(v.st, scratch, n, d, (c->flags & KM_FLAG_SPHERICAL) ? 1 : 0, c->stream));
+    KM_HIP(km::launch_set_scales(v.st, scratch, n, d, (c->flags & KM_FLAG_SPHERICAL) ? 1 : 0, x2part, nx2, x2sum,
+                                 c->stream));
     if (c->flags & (KM_FLAG_VALIDATE | KM_FLAG_SPHERICAL)) {
         uint32_t host[5];
         int32_t* pin = pinned_take();
@@ -1287,6 +1300,7 @@ const char* kmeans_mti_path(const km_ctx* ctx) {
     if (!ctx) return "";
     if (ctx->small) return ctx->inc ? "stream-d16" : "stream-d16-full";
     if (ctx->large) return "global-mfma";
+    if (ctx->gen == km::kGenMat && ctx->k > 16 && ctx->k <= 128 && (ctx->d == 16 || ctx->d == 32)) return "lds-mfma";
     if (ctx->incmm || ctx->gen == km::kGenMat) return "lds-inc";
     if (ctx->gen == km::kGenVec) return "lds-vector";
     if (ctx->variant % 16 == 8) return "lds-elkan";

@@ -180,4 +180,56 @@ __device__ inline uint64_t wave_sum_u64(uint64_t v) {
     return v;
 }
 
+// Double-double sums (an unevaluated sum h + l, error about 2^-104 of it):
+// the inertia is the difference of two sums that may be far larger.
+struct DD {
+    double h, l;
+};
+__device__ __forceinline__ DD dd_add(DD a, double b) {   // two-sum (Knuth), the error kept in l
+    const double s = a.h + b, t = s - a.h;
+    const double e = (a.h - (s - t)) + (b - t) + a.l;
+    const double r = s + e;
+    return DD{r, e - (r - s)};
+}
+__device__ __forceinline__ DD dd_add(DD a, DD b) { return dd_add(dd_add(a, b.l), b.h); }
+__device__ __forceinline__ DD dd_fma(DD a, double x, double y) {   // a + x y
+    const double p = x * y;
+    return dd_add(dd_add(a, fma(x, y, -p)), p);
+}
+// v (exact) as a double-double.
+__device__ __forceinline__ DD dd_int(int64_t v) {
+    const double h = (double)(v >> 32) * 0x1p32;
+    return dd_add(DD{h, 0.0}, (double)(v & 0xffffffffll));
+}
+__device__ __forceinline__ DD dd_wave_sum(DD a) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) a = dd_add(a, DD{__shfl_xor(a.h, o), __shfl_xor(a.l, o)});
+    return a;
+}
+
+// The inertia of the step that has just ended, by the first wave of a block:
+// sum |x|^2 + sum_j (n_j |c_j|^2 - 2 c_j . S_j), the cluster terms as the
+// fixed-point integers k_update left (their sum does not depend on the
+// order of the clusters).
+__device__ inline void close_inertia(const Dev& P) {
+    IterState* st = P.st;
+    int64_t hi = 0, lo = 0;
+    for (int j = threadIdx.x; j < P.k; j += 64) {
+        hi += P.iterm[2 * j];
+        lo += P.iterm[2 * j + 1];
+    }
+    hi = (int64_t)wave_sum_u64((uint64_t)hi);
+    lo = (int64_t)wave_sum_u64((uint64_t)lo);
+    if (threadIdx.x == 0) {
+        DD v = dd_add(dd_int(hi), (double)lo * 0x1p-40);
+        v = DD{v.h * st->iinv, v.l * st->iinv};
+        v = dd_add(v, DD{P.x2sum[0], P.x2sum[1]});
+        const double r = v.h + v.l;
+        // within the terms' rounding: zero (every point on its centroid)
+        const double inertia = fabs(r) <= P.k * st->iinv * 0x1p-40 || r < 0.0 ? 0.0 : r;
+        st->inertia_last = inertia;
+        P.rec[(st->t - 1) % kHistCap].inertia = inertia;
+    }
+}
+
 }  // namespace km

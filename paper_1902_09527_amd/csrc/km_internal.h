@@ -76,6 +76,8 @@ struct Dev {
     uint64_t* sums;       // incremental path: k*d + k exact sums and counts, carried across steps (else null)
     float* hm;            // incremental path: k x 4, min over centroid block cb of h[a][j] (h[a][a] = 0), else null
     uint64_t* rows;       // general incremental path: kGenRows x L accumulation rows (zero between steps), else null
+    int64_t* iterm;       // inertia (general incremental and global paths): 2 k fixed-point terms of the step (k_update), else null
+    const double* x2sum;  // sum of all |x|^2 (set-up), as an unevaluated sum of two doubles, else null
     uint64_t* part;       // G x L per-block partial rows
     uint64_t* total;      // L reduced row (zero between iterations)
     IterState* st;
@@ -131,7 +133,6 @@ struct Large {
     uint32_t* cbase;      // k + 1 first segment chunk of each cluster
     int32_t* perm;        // n point indices grouped by cluster
     uint64_t* cpart;      // NCmax x d chunk partial sums (fixed point)
-    uint64_t* ciq;        // NCmax chunk inertia partials (fixed point)
     uint32_t* xs;         // n split rows of X (set-up)
     float* x2;            // n: float32 squared norms of the rows of X (set-up)
     float* sx2;           // n: x2 of the survivors, in list order
@@ -396,8 +397,11 @@ hipError_t large_set_attributes(int k, int d);
 // about 1024 values), as float bits (atomic max; NaN ignored, an infinite
 // value counted as the largest float), and whether a or b holds a
 // non-finite value.
+// x2part (nullable): the blocks of a write their sums of squares there, two
+// doubles each (absmax_blocks(na, cus) of them).
 hipError_t launch_absmax(const float* a, int64_t na, const float* b, int64_t nb, const float* x, int64_t n,
-                         int32_t d, int cus, uint32_t* out, hipStream_t s);
+                         int32_t d, int cus, uint32_t* out, double* x2part, hipStream_t s);
+int absmax_blocks(int64_t na, int cus);
 
 // Buffers cleared and the loop state written by one set-up launch.
 struct ZeroRanges {
@@ -423,7 +427,9 @@ struct ZeroRanges {
 hipError_t launch_init_buffers(const ZeroRanges& z, int cus, hipStream_t s);
 // Fixed-point scales into st from the largest |x| and |c0| (float bits in
 // absmax[0] and absmax[2]; unit = 1: spherical k-means, centroids of norm 1).
-hipError_t launch_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d, int unit, hipStream_t s);
+// x2part (nullable): nx2 pairs summed into x2sum.
+hipError_t launch_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d, int unit,
+                             const double* x2part, int nx2, double* x2sum, hipStream_t s);
 hipError_t launch_set_centroids(const float* C0, double* C64, float* C32, float* ec, int64_t kd,
                                 int32_t k, hipStream_t s);
 // Spherical k-means: rows of X projected to the unit sphere into Xn; unit

@@ -83,9 +83,19 @@ __device__ __forceinline__ void absmax_take(float v, uint32_t& m, uint32_t& bad)
 constexpr int kAbsLoads = 8;
 constexpr int kAbsBlocksPerCU = 1;
 constexpr int kAbsSampleChunks = 16;
+// SQ: also the sum of squares (each square exact in float64), four chains.
+template <bool SQ>
 __device__ __forceinline__ void absmax_range(const float* __restrict__ p, int64_t count, int64_t t0,
-                                             int64_t stride, uint32_t& m, uint32_t& bad) {
-    auto take = [&](float v) __attribute__((always_inline)) { absmax_take(v, m, bad); };
+                                             int64_t stride, uint32_t& m, uint32_t& bad, DD& sq) {
+    DD s4[4] = {};
+    int ch = 0;
+    auto take = [&](float v) __attribute__((always_inline)) {
+        absmax_take(v, m, bad);
+        if constexpr (SQ) {
+            s4[ch] = dd_add(s4[ch], (double)v * (double)v);
+            ch = (ch + 1) & 3;   // a constant in the unrolled loops
+        }
+    };
     const int64_t nq = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? count / 4 : 0;
     const f32x4* __restrict__ q = reinterpret_cast<const f32x4*>(p);
     int64_t i = t0;
@@ -108,7 +118,11 @@ __device__ __forceinline__ void absmax_range(const float* __restrict__ p, int64_
         take(v.z);
         take(v.w);
     }
-    for (int64_t j = 4 * nq + t0; j < count; j += stride) take(p[j]);
+    for (int64_t j = 4 * nq + t0; j < count; j += stride) {
+        ch = 0;
+        take(p[j]);
+    }
+    if constexpr (SQ) sq = dd_add(dd_add(s4[0], s4[1]), dd_add(s4[2], s4[3]));
 }
 
 // Three roles in one launch: blocks [0, blocks_a) scan a (out[kAmaxX],
@@ -118,17 +132,32 @@ __device__ __forceinline__ void absmax_range(const float* __restrict__ p, int64_
 // cut at n (out[kAmaxSample]).  whole: the sample holds every row (n <= C
 // times the rows per chunk) and a is x: no sample blocks, the scan of a
 // writes both words.  All words zero before the launch.
+template <bool SQ>
 __global__ __launch_bounds__(256) void k_absmax(const float* __restrict__ a, int64_t na, const float* __restrict__ b,
                                                int64_t nb, int blocks_a, int blocks_b, const float* __restrict__ x,
-                                               int64_t n, int32_t d, int whole, uint32_t* out) {
+                                               int64_t n, int32_t d, int whole, uint32_t* out,
+                                               double* __restrict__ x2part) {
     const int bi = (int)blockIdx.x;
     const int role = bi < blocks_a ? 0 : (bi < blocks_a + blocks_b ? 1 : 2);
     uint32_t m = 0, bad = 0;
-    if (role < 2) {
-        const int blk = role == 0 ? bi : bi - blocks_a;
-        const int nblk = role == 0 ? blocks_a : blocks_b;
-        absmax_range(role == 0 ? a : b, role == 0 ? na : nb, (int64_t)blk * blockDim.x + threadIdx.x,
-                     (int64_t)nblk * blockDim.x, m, bad);
+    if (role == 0) {
+        DD sq{};
+        absmax_range<SQ>(a, na, (int64_t)bi * blockDim.x + threadIdx.x, (int64_t)blocks_a * blockDim.x, m, bad, sq);
+        if constexpr (SQ) {
+            __shared__ DD ws[4];
+            sq = dd_wave_sum(sq);
+            if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sq;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                sq = dd_add(dd_add(ws[0], ws[1]), dd_add(ws[2], ws[3]));
+                x2part[2 * bi] = sq.h;
+                x2part[2 * bi + 1] = sq.l;
+            }
+        }
+    } else if (role == 1) {
+        DD none;
+        absmax_range<false>(b, nb, (int64_t)(bi - blocks_a) * blockDim.x + threadIdx.x, (int64_t)blocks_b * blockDim.x,
+                            m, bad, none);
     } else {
         const int64_t c = bi - blocks_a - blocks_b;
         const int64_t r0 = c * n / kAbsSampleChunks;
@@ -188,7 +217,17 @@ __global__ __launch_bounds__(256) void k_init_buffers(ZeroRanges z) {
 // those of the sample's bound, and the end of the first step sets them again
 // from the word that step wrote (its sums corrected first when X exceeded
 // the bound).
-__global__ void k_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d, int unit) {
+__global__ __launch_bounds__(64) void k_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d,
+                                                   int unit, const double* x2part, int nx2, double* x2sum) {
+    if (x2part) {
+        DD s{};
+        for (int i = threadIdx.x; i < nx2; i += 64) s = dd_add(s, DD{x2part[2 * i], x2part[2 * i + 1]});
+        s = dd_wave_sum(s);
+        if (threadIdx.x == 0) {
+            x2sum[0] = s.h;
+            x2sum[1] = s.l;
+        }
+    }
     if (threadIdx.x != 0) return;
     const float cmax = unit ? 1.0f : __uint_as_float(absmax[kAmaxC]);
     put_scales(st, sum_exp(absmax), cmax, n, d);
@@ -292,6 +331,7 @@ __global__ __launch_bounds__(64) void k_set_centroids_unit(const float* __restri
 __global__ __launch_bounds__(256) void k_centroid_table(Dev P, int force) {
     if (!force && !P.st->active) return;
     const int i = blockIdx.x, k = P.k, d = P.d, tid = threadIdx.x, lane = tid & 63;
+    if (P.iterm && !force && i == 0 && tid < 64) close_inertia(P);
     const double* ci = P.C64 + (int64_t)i * d;
     __shared__ float hrow[kIMMaxK], red[4], redm[4];
     const int G = d <= 4 ? 1 : d <= 8 ? 2 : d <= 16 ? 4 : d <= 32 ? 8 : 16;
@@ -1291,6 +1331,9 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
         else keep = true;
     }
     double dr = 0.0, de = 0.0;
+    // The cluster's inertia term sum over members of |c|^2 - 2 c.x with the
+    // centroid c the step used, from the exact sums: no member's row is read.
+    DD term{};
     for (int m = threadIdx.x; m < d; m += 64) {
         const int64_t o = (int64_t)j * d + m;
         const double cold = m < 64 ? cold0 : P.C64[o];
@@ -1298,6 +1341,14 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
         const double cnew = keep ? cold : mean(tv) / scale;
         if (P.sums) P.sums[o] = tv;
         clear(o);
+        if (P.iterm) {   // c (n c - 2 S)
+            const DD S = dd_int((int64_t)(tv - count * kMagicBits));
+            const double nc = (double)count * cold;
+            term = dd_fma(term, cold, nc);
+            term = dd_fma(term, cold, fma((double)count, cold, -nc));
+            term = dd_fma(term, cold, -2.0 * P.qinv * S.h);
+            term = dd_fma(term, cold, -2.0 * P.qinv * S.l);
+        }
         const double df = cnew - cold;
         dr = fma(df, df, dr);
         const float c32 = (float)cnew;
@@ -1310,6 +1361,16 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
     for (int off = 32; off > 0; off >>= 1) {
         dr += __shfl_xor(dr, off);
         de += __shfl_xor(de, off);
+    }
+    if (P.iterm) {
+        term = dd_wave_sum(term);
+        if (threadIdx.x == 0) {   // as 2^SI (h + l 2^-40), l in [0, 2^40)
+            const double t = term.h * P.iscale;
+            const double h = floor(t);
+            const DD rest = dd_add(DD{t - h, 0.0}, term.l * P.iscale);
+            P.iterm[2 * j] = (int64_t)h;
+            P.iterm[2 * j + 1] = (int64_t)rint((rest.h + rest.l) * 0x1p40);
+        }
     }
     if (threadIdx.x == 0) {
         P.f[j] = f32_up(sqrt(dr) * (1.0 + 0x1p-40));
@@ -1342,7 +1403,8 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
         const int64_t rc = (int64_t)sc[kStRecheck];
         const int64_t iq = (int64_t)sc[kStInertia];
         for (int c = 0; c < kNumStat; ++c) sc[c] = 0;
-        const double inertia = (P.flags & KM_FLAG_STATS) ? (double)iq * P.iinv : NAN;
+        // with iterm written by the centroid table (close_inertia)
+        const double inertia = (P.flags & KM_FLAG_STATS) && !P.iterm ? (double)iq * P.iinv : NAN;
         const int t = st->t;
         IterRec& r = P.rec[t % kHistCap];
         r.changed = changed;
@@ -1389,25 +1451,33 @@ const void* assign_kernel_symbol(int variant) {
     }
 }
 
+int absmax_blocks(int64_t na, int cus) {
+    const int64_t ba = (na + 4 * 4 * 256 - 1) / (4 * 4 * 256);
+    return (int)(ba > kAbsBlocksPerCU * (int64_t)cus ? kAbsBlocksPerCU * (int64_t)cus : ba);
+}
+
 hipError_t launch_absmax(const float* a, int64_t na, const float* b, int64_t nb, const float* x, int64_t n,
-                         int32_t d, int cus, uint32_t* out, hipStream_t s) {
+                         int32_t d, int cus, uint32_t* out, double* x2part, hipStream_t s) {
     if (na < 0 || nb < 1 || n < 1 || d < 1) return hipErrorInvalidValue;
     // a (X): up to kAbsBlocksPerCU blocks per CU (none when na = 0); b (C0):
     // a few blocks; then the sample's chunks.
-    int64_t ba = (na + 4 * 4 * 256 - 1) / (4 * 4 * 256);
-    if (ba > kAbsBlocksPerCU * (int64_t)cus) ba = kAbsBlocksPerCU * (int64_t)cus;
+    const int64_t ba = absmax_blocks(na, cus);
     int64_t bb = (nb + 4 * 4 * 256 - 1) / (4 * 4 * 256);
     if (bb > 64) bb = 64;
     if (bb < 1) bb = 1;
     const int64_t rows = d >= 1024 ? 1 : 1024 / d;
     const int whole = na == n * d && a == x && n <= kAbsSampleChunks * rows ? 1 : 0;
-    hipLaunchKernelGGL(k_absmax, dim3((unsigned)(ba + bb + (whole ? 0 : kAbsSampleChunks))), dim3(256), 0, s, a, na,
-                       b, nb, (int)ba, (int)bb, x, n, d, whole, out);
+    const dim3 grid((unsigned)(ba + bb + (whole ? 0 : kAbsSampleChunks))), block(256);
+    if (x2part)
+        hipLaunchKernelGGL(k_absmax<true>, grid, block, 0, s, a, na, b, nb, (int)ba, (int)bb, x, n, d, whole, out, x2part);
+    else
+        hipLaunchKernelGGL(k_absmax<false>, grid, block, 0, s, a, na, b, nb, (int)ba, (int)bb, x, n, d, whole, out, x2part);
     return hipGetLastError();
 }
 
-hipError_t launch_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d, int unit, hipStream_t s) {
-    hipLaunchKernelGGL(k_set_scales, dim3(1), dim3(64), 0, s, st, absmax, n, d, unit);
+hipError_t launch_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d, int unit,
+                             const double* x2part, int nx2, double* x2sum, hipStream_t s) {
+    hipLaunchKernelGGL(k_set_scales, dim3(1), dim3(64), 0, s, st, absmax, n, d, unit, x2part, nx2, x2sum);
     return hipGetLastError();
 }
 

@@ -20,8 +20,8 @@
 //   k_scan_large_clusters  cluster starts and per-block write offsets;
 //   k_scatter_large     point indices grouped by cluster (counting sort);
 //   k_segsum_large      exact fixed-point sums over chunks of each cluster;
-//   k_chunk_reduce_large  per-cluster sums, counts and the inertia into the
-//                       reduced row read by k_update;
+//   k_chunk_reduce_large  per-cluster sums and counts into the reduced row
+//                       read by k_update;
 //   k_centroid_table_tiled  half centroid distances for the next step;
 //   k_split_rows        split operand rows of the new centroids with their
 //                       squared norms and the per-centroid minimum s of the
@@ -66,10 +66,9 @@ __device__ __forceinline__ void add_stats_block(uint64_t* total, const int (&slo
 
 // The step's per-cluster sums come from its moves (added to the running
 // sums kept by k_update) when few points moved; otherwise from the counting
-// sort and exact segment sums.  The first step, and steps that gather the
-// inertia, always take the full sums.
+// sort and exact segment sums.  The first step always takes the full sums.
 __device__ __forceinline__ bool large_incremental(const Dev& P, const Large& Lg) {
-    return P.st->t > 0 && !(P.flags & KM_FLAG_STATS) && *Lg.nmv <= (uint32_t)Lg.mvcap;
+    return P.st->t > 0 && *Lg.nmv <= (uint32_t)Lg.mvcap;
 }
 
 }  // namespace
@@ -602,7 +601,7 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
         __syncthreads();
     };
 
-    const bool rec_moves = !first && !(P.flags & KM_FLAG_STATS);
+    const bool rec_moves = !first;
     // A block takes runs of kRefineFlush list entries (rpf rounds), neighbours
     // in the list being neighbours in the point arrays.  A round's loads are
     // requested a round ahead (two ahead took as long); the buffers are looked
@@ -690,7 +689,8 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
         // One candidate is the nearest centroid (every other one is certified
         // farther): as on the LDS paths, its bound then comes from its
         // expanded value and the error bound, without the direct form (kept
-        // when statistics are gathered).  Otherwise the survivor and its
+        // when statistics are gathered: their Clause-1 counts are then those
+        // of the direct form's bounds).  Otherwise the survivor and its
         // candidates go to k_multi_large.
         const bool single = !full && nq == 1 && !(P.flags & KM_FLAG_STATS);
         const bool queued = live && !full && !single;
@@ -768,7 +768,7 @@ __global__ __launch_bounds__(256) void k_multi_large(Dev P, Large Lg) {
     if (!st->active) return;
     const int k = P.k, d = P.d, lane = threadIdx.x & 63;
     const bool first = st->t == 0;
-    const bool rec_moves = !first && !(P.flags & KM_FLAG_STATS);
+    const bool rec_moves = !first;
     const float gamma = P.gamma, ecm = st->ec_max;
     const uint32_t nq_all = *Lg.nmq;
     const bool vec = (d & 3) == 0;
@@ -894,7 +894,7 @@ __global__ __launch_bounds__(256) void k_full_large(Dev P, Large Lg) {
     if (!st->active) return;
     const int k = P.k, d = P.d;
     const bool first = st->t == 0;
-    const bool rec_moves = !first && !(P.flags & KM_FLAG_STATS);
+    const bool rec_moves = !first;
     const uint32_t nf = *Lg.nfull;
     const uint32_t nsplit = min(nf, (uint32_t)kFullCap);
     const int kr = (k + kFullSplit - 1) / kFullSplit;
@@ -1080,8 +1080,7 @@ __global__ __launch_bounds__(256) void k_scatter_large(Dev P, Large Lg) {
 }
 
 // One block per chunk of <= kLgChunkRows points of one cluster: exact
-// fixed-point coordinate sums (and, with KM_FLAG_STATS, the squared
-// distances to the cluster's current centroid, element by element).
+// fixed-point coordinate sums.
 __global__ __launch_bounds__(256) void k_segsum_large(Dev P_, Large Lg) {
     const Dev P = with_scales(P_);
     if (!P.st->active || large_incremental(P, Lg)) return;
@@ -1097,33 +1096,15 @@ __global__ __launch_bounds__(256) void k_segsum_large(Dev P_, Large Lg) {
     const int j = lo;
     const uint32_t r0 = Lg.base[j] + (uint32_t)(c - (int)Lg.cbase[j]) * kLgChunkRows;
     const uint32_t r1 = min(Lg.base[j + 1], r0 + kLgChunkRows);
-    const bool want_inertia = (P.flags & KM_FLAG_STATS) != 0;
-    uint64_t iq = 0;
     for (int m = threadIdx.x; m < d; m += blockDim.x) {
-        const float cj = P.C32[(int64_t)j * d + m];
         uint64_t acc = 0;
-        for (uint32_t r = r0; r < r1; ++r) {
-            const float x = P.X[(int64_t)Lg.perm[r] * d + m];
-            acc += fixed_bits((double)x, P.qscale);
-            if (want_inertia) {
-                const float t = x - cj;
-                iq += fixed_bits((double)(t * t), P.iscale) - kMagicBits;
-            }
-        }
+        for (uint32_t r = r0; r < r1; ++r) acc += fixed_bits((double)P.X[(int64_t)Lg.perm[r] * d + m], P.qscale);
         Lg.cpart[(int64_t)c * d + m] = acc;
-    }
-    if (want_inertia) {
-        __shared__ uint64_t rs[4];
-        iq = wave_sum_u64(iq);
-        if ((threadIdx.x & 63) == 0) rs[threadIdx.x >> 6] = iq;
-        __syncthreads();
-        if (threadIdx.x == 0) Lg.ciq[c] = rs[0] + rs[1] + rs[2] + rs[3];
     }
 }
 
 // Per-cluster sums (over the cluster's chunks) and counts into the reduced
-// row, less the running sums that k_update adds back; block 0 also adds the
-// inertia partials.
+// row, less the running sums that k_update adds back.
 __global__ __launch_bounds__(256) void k_chunk_reduce_large(Dev P, Large Lg) {
     if (!P.st->active || large_incremental(P, Lg)) return;
     const int k = P.k, d = P.d;
@@ -1137,16 +1118,6 @@ __global__ __launch_bounds__(256) void k_chunk_reduce_large(Dev P, Large Lg) {
             const int64_t o = (int64_t)k * d + j;
             P.total[o] = (uint64_t)(Lg.base[j + 1] - Lg.base[j]) - P.sums[o];
         }
-    }
-    if (blockIdx.x == 0 && (P.flags & KM_FLAG_STATS)) {
-        __shared__ uint64_t rs[4];
-        uint64_t s = 0;
-        const uint32_t nc = Lg.cbase[k];
-        for (uint32_t cc = threadIdx.x; cc < nc; cc += blockDim.x) s += Lg.ciq[cc];
-        s = wave_sum_u64(s);
-        if ((threadIdx.x & 63) == 0) rs[threadIdx.x >> 6] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) P.total[(int64_t)k * d + k + kStInertia] = rs[0] + rs[1] + rs[2] + rs[3];
     }
 }
 
@@ -1187,6 +1158,7 @@ __global__ __launch_bounds__(256) void k_centroid_table_tiled(Dev P, Large Lg, i
         *Lg.nmq = 0;
         *Lg.nmv = 0;
     }
+    if (P.iterm && !force && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64) close_inertia(P);
     const int k = P.k, d = P.d;
     const int i0 = blockIdx.x * kTiTile, ni = min(kTiTile, k - i0);
     // Block column y takes centroids j in [y k / kTiSplit, (y + 1) k / kTiSplit).

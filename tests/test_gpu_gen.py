@@ -109,3 +109,29 @@ def test_general_step_with_infinite_and_nan_rows_ends():
     X[9, 0] = np.nan
     a, _, st = km.run(_gpu(X), _gpu(C0), 5)
     assert st["iterations"] == 5 and int(a.min()) >= 0 and int(a.max()) < 12
+
+
+@pytest.mark.parametrize("n,d,k,kw", [(3001, 7, 9, {}), (3000, 24, 40, {}), (3000, 32, 40, {}), (5000, 64, 200, {}),
+                                      (2000, 33, 300, {}), (3000, 24, 20, {"spherical": True}), (300, 20, 300, {})],
+                         ids=lambda v: str(v))
+def test_inertia_from_exact_sums(n, d, k, kw):
+    # sum |x|^2 + sum_j (n_j |c_j|^2 - 2 c_j . S_j): the sums are exact images
+    # within 2^-50 of max |x| per value, everything else is carried in double
+    # pairs, so the inertia is within about 2^-48 of sum |x|^2 (1e-12 of it
+    # here; sum |x|^2 is below 100 times the inertia for k << n).
+    X, C0 = synth.blobs(n, d, k, seed=841 + d, spread=4.0, sigma=1.5, comps=min(k, 30))
+    if k == n:
+        C0 = X.copy()
+    Y = X.astype(np.float64)
+    if kw:
+        Y = (Y / np.linalg.norm(Y, axis=1, keepdims=True)).astype(np.float32).astype(np.float64)
+    with km.KMeansMTI(_gpu(X), _gpu(C0), stats=True, **kw) as ctx:
+        for _ in range(5):
+            c = ctx.centroids64()
+            ctx.iterate()
+            a, _ = ctx.get(centroids=False)
+            want = ((Y - c[a.cpu().numpy()]).astype(np.longdouble) ** 2).sum()
+            assert abs(float(ctx.stats()["inertia_last"] - want)) <= 1e-12 * max(float(want), 1e-2 * (Y ** 2).sum())
+        assert ctx.history()["inertia"][-1] == ctx.stats()["inertia_last"]
+        if k == n:
+            assert ctx.stats()["inertia_last"] == 0.0
