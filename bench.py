@@ -29,7 +29,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 MFMA_F32_PEAK_TFS = 157.3   # MI355X dense float32 matrix peak
-MFMA_BF16_PEAK_TFS = 2500.0  # MI355X dense bf16 matrix peak (the split products of k_mfma_large, k_inc_mm)
+MFMA_BF16_PEAK_TFS = 2500.0  # MI355X dense bf16 matrix peak (the split products of k_mfma_large, k_inc_mat)
 DEFAULT_WORKLOAD = "aniso-8M-d16-k10"
 METRIC = "k-means iters/sec + effective dist evals/sec; % HBM peak (low d) / % MFMA (big k·d)"
 
@@ -40,7 +40,7 @@ def log(msg: str) -> None:
 
 # Dominant (assignment-step) kernel of each library path.
 DOMINANT_KERNEL = {"stream-d16": "k_inc", "stream-d16-full": "k_small", "lds-vector": "k_assign",
-                   "lds-mfma": "k_assign", "lds-elkan": "k_assign", "lds-inc": "k_inc_mm",
+                   "lds-mfma": "k_assign", "lds-elkan": "k_assign", "lds-inc": "k_inc_mat",
                    "global-mfma": "k_mfma_large"}
 # Sources of each dominant kernel: the hardware byte counts of a committed
 # profile summary are used only while these files are unchanged.
@@ -50,7 +50,7 @@ KERNEL_SOURCES = {
     "k_inc": ["km_small.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
     "k_first": ["km_small.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
     "k_assign": ["km_kernels.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
-    "k_inc_mm": ["km_incmm.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
+    "k_inc_mat": ["km_gen.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
     "k_mfma_large": ["km_large.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
     "k_pp_step": ["km_pp.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
 }
@@ -476,7 +476,7 @@ def main() -> int:
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "bf16x3+f32" if path in ("global-mfma", "lds-inc") else "f32",
+        "dtype": "bf16x3+f32" if path == "global-mfma" else "f16x3+f32" if path == "lds-inc" else "f32",
         "data": "synthetic",
         "config": {"workload": w.name, "method": ("spherical" if args.spherical else "kmeans") +
                    ("+elkan-ti" if args.elkan else ""),

@@ -82,8 +82,7 @@ enum {
                                   read of X) in every step instead of moving the sums of the
                                   points whose assignment changed, where only the Clause-1
                                   survivors' rows are read after the first step (the
-                                  streaming path, d = 16 and k <= 16, and the incremental
-                                  matrix-core path, d = 16 or 32 and k <= 128); same results.
+                                  streaming path and the incremental paths); same results.
                                   On the streaming path implied by KM_FLAG_STATS. */
     KM_FLAG_SPHERICAL = 256u,  /* spherical k-means (the paper's sk-means application): the
                                   rows of X are projected to the unit sphere (into a copy the
@@ -203,13 +202,10 @@ int kmeans_mti_run(const float* X, int64_t n, int32_t d, int32_t k, const float*
  * survivors' rows are read, one lane per survivor; then k_update,
  * k_centroid_table), "lds-inc" (only the states and the survivors' rows are
  * read, the survivors are settled on the matrix cores and the moves of the
- * points whose cluster changed are summed: k_inc_mm for d = 16 or 32 and k <=
- * 128, then k_reduce, k_update, k_centroid_table; k_inc_mat for other d and k
- * <= 256 while its tables fit in LDS, then k_update, k_centroid_table; with
- * KM_FLAG_STATS k_inc_mat also takes d = 16 or 32, reported as "lds-mfma" for
- * 16 < k <= 128),
- * "lds-elkan" (the
- * general kernel with KM_FLAG_ELKAN's lower-bound scan), "global-mfma"
+ * points whose cluster changed are summed: k_inc_mat, k <= 256 while its tables
+ * fit in LDS, then k_update, k_centroid_table; with KM_FLAG_STATS reported as
+ * "lds-mfma" for d = 16 or 32 and 16 < k <= 128), "lds-elkan" (the general
+ * kernel with KM_FLAG_ELKAN's lower-bound scan), "global-mfma"
  * (centroids or sums too large for LDS: dense MFMA survivors, sums by
  * counting sort).  "" for a NULL context.
  */

@@ -185,8 +185,6 @@ struct km_ctx {
     bool large = false;   // global-memory path (centroids / sums too large for LDS)
     bool small = false;   // streaming step (d = 16, k <= 16)
     bool inc = false;     // ... with incremental steps after the first
-    bool incmm = false;   // incremental matrix-core step (d = 16 or 32, k <= 128)
-    int gim = 0, lds_im = 0;   // its grid and LDS
     km::GenKind gen = km::kGenNone;   // general incremental step (any d)
     int gg = 0, gsub = 1, lds_gen = 0;   // its grid, 64-point sub-steps per wave tile and LDS
     int gi = 0, lds_inc = 0;   // grid and LDS of the incremental kernel
@@ -335,7 +333,6 @@ int enqueue_iteration(km_ctx* c) {
         return KM_OK;
     }
     e = c->gen     ? km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, c->enq == 0 ? 1 : 0, c->stream)
-        : c->incmm ? km::launch_inc_mm(c->dv, c->gim, c->lds_im, c->enq == 0 ? 1 : 0, c->stream)
         : c->large ? km::launch_large_assign(c->dv, c->lg, c->gb, c->stream)
                    : km::launch_assign(c->dv, c->variant, c->tp, c->lds, c->stream);
     if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "assign kernel"));
@@ -494,39 +491,23 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
             c->gi = (int)gi;
         }
     } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY |
-                                         KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE | KM_FLAG_STATS)) &&
-               km::inc_mm_applies(n, d, k, aligned) && km::inc_mm_lds(d, km::inc_mm_kb(k)).bytes <= max_lds) {
-        // Incremental matrix-core step: only the Clause-1 survivors' rows are read.
-        c->incmm = true;
-        c->lds_im = km::inc_mm_lds(d, km::inc_mm_kb(k)).bytes;
-        const void* sym = km::inc_mm_symbol(d, k);
-        int per_cu = 0, rcc;
-        if ((rcc = kernel_config(c->device, sym, km::kIMWaves * 64, c->lds_im, &per_cu)) != KM_OK) return rcc;
-        if (per_cu < 1) return KM_ERR_UNSUPPORTED;
-        // Resident blocks, at most one wave tile per wave.
-        const int64_t nwt = (n + km::kIMTile - 1) / km::kIMTile;
-        int64_t G = (int64_t)per_cu * cus;
-        const int64_t want = (nwt + km::kIMWaves - 1) / km::kIMWaves;
-        if (G > want) G = want > 0 ? want : 1;
-        c->gim = (int)G;
-        v.G = (int32_t)G;
-    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY |
                                          KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE)) &&
                (c->gen = km::gen_kind(n, d, k, max_lds)) != km::kGenNone) {
         // General incremental step: resident blocks, at most one wave tile
         // per wave, small inputs spread over up to one block per CU.
         c->lds_gen = km::gen_lds_bytes(c->gen, d, k);
+        const int gw = km::gen_waves(c->gen, d, k);
         int per_cu = 0, rcc;
-        if ((rcc = kernel_config(c->device, km::gen_symbol(c->gen, v), km::kGenThreads, c->lds_gen, &per_cu)) != KM_OK)
+        if ((rcc = kernel_config(c->device, km::gen_symbol(c->gen, v), 64 * gw, c->lds_gen, &per_cu)) != KM_OK)
             return rcc;
         if (per_cu < 1) return KM_ERR_UNSUPPORTED;
         // Wave tiles of 256 points, less where that would leave waves
         // without one: what a step of a small input takes is the longest
         // wave's chain of batches.
         const int64_t G = (int64_t)per_cu * cus, n64 = (n + 63) / 64;
-        c->gsub = n64 >= 4 * G * km::kGenWaves ? 4 : n64 >= 2 * G * km::kGenWaves ? 2 : 1;
+        c->gsub = n64 >= 4 * G * gw ? 4 : n64 >= 2 * G * gw ? 2 : 1;
         const int64_t nwt = (n64 + c->gsub - 1) / c->gsub;
-        int64_t want = (nwt + km::kGenWaves - 1) / km::kGenWaves;
+        int64_t want = (nwt + gw - 1) / gw;
         if (want < cus) want = nwt < cus ? nwt : cus;
         c->gg = (int)(G < want ? G : want);
         v.G = 1;
@@ -547,7 +528,7 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
             }
         }
     }
-    if (c->small || c->incmm || c->gen) {
+    if (c->small || c->gen) {
         // configured above
     } else if (c->tp > 0) {
         const void* sym = km::assign_kernel_symbol(c->variant);
@@ -613,31 +594,16 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
     }
 
     int rc;
-    if (!c->small && !c->incmm && !c->gen && ((rc = c->alloc(&v.a, (size_t)n)) || (rc = c->alloc(&v.u, (size_t)n))))
+    if (!c->small && !c->gen && ((rc = c->alloc(&v.a, (size_t)n)) || (rc = c->alloc(&v.u, (size_t)n))))
         return rc;
-    if (c->incmm) {   // point states padded to whole wave tiles, running sums, cumulative drifts
-        const size_t nw = (size_t)((n + km::kIMTile - 1) / km::kIMTile) * km::kIMTile;
-        if ((rc = c->alloc(&v.w, nw)) || (rc = c->alloc(&v.sums, (size_t)k * d + k)) ||
-            (rc = c->alloc(&v.dhi, (size_t)k)) || (rc = c->alloc(&v.dlo, (size_t)k)) ||
-            (rc = c->alloc(&v.dupf, (size_t)k)) || (rc = c->alloc(&v.ddnf, (size_t)k)) ||
-            (rc = c->alloc(&v.hm, (size_t)4 * k)))
-            return rc;
-        const size_t n4 = (size_t)n & ~(size_t)3;   // states are written by the first step; padding cleared
-        zr.add(v.w + n4, sizeof(uint32_t) * (nw - n4));
-        zr.add(v.sums, sizeof(uint64_t) * ((size_t)k * d + k));
-        zr.add(v.dhi, sizeof(double) * (size_t)k);
-        zr.add(v.dlo, sizeof(double) * (size_t)k);
-        zr.add(v.dupf, sizeof(float) * (size_t)k);
-        zr.add(v.ddnf, sizeof(float) * (size_t)k);
-    }
-    if (c->gen) {   // as above, with accumulation rows instead of partial rows
+    if (c->gen) {   // point states padded to whole wave tiles, running sums, accumulation rows, cumulative drifts
         const size_t nw = (size_t)((n + km::kGenTile - 1) / km::kGenTile) * km::kGenTile;
         if ((rc = c->alloc(&v.w, nw)) || (rc = c->alloc(&v.sums, (size_t)k * d + k)) ||
             (rc = c->alloc(&v.rows, (size_t)km::kGenRows * v.L)) || (rc = c->alloc(&v.dhi, (size_t)k)) ||
             (rc = c->alloc(&v.dlo, (size_t)k)) || (rc = c->alloc(&v.dupf, (size_t)k)) ||
-            (rc = c->alloc(&v.ddnf, (size_t)k)))
+            (rc = c->alloc(&v.ddnf, (size_t)k)) || (c->gen == km::kGenMat && k > 64 && k <= km::kTabMinK && (rc = c->alloc(&v.hm, (size_t)4 * k))))
             return rc;
-        const size_t n4 = (size_t)n & ~(size_t)3;
+        const size_t n4 = (size_t)n & ~(size_t)3;   // states are written by the first step; padding cleared
         zr.add(v.w + n4, sizeof(uint32_t) * (nw - n4));
         zr.add(v.sums, sizeof(uint64_t) * ((size_t)k * d + k));
         zr.add(v.rows, sizeof(uint64_t) * (size_t)km::kGenRows * v.L);
@@ -882,12 +848,10 @@ static int get_outputs(km_ctx* ctx, int32_t* assign_out, float* C_out) {
     if (assign_out && ctx->small &&
         (e = km::launch_small_unpack(ctx->fz, ctx->n, assign_out, ctx->stream)) != hipSuccess)
         return fail_ctx(ctx, hip_fail(e, "assignment unpack kernel"));
-    if (assign_out && ctx->incmm && (e = km::launch_inc_mm_unpack(ctx->dv, assign_out, ctx->stream)) != hipSuccess)
-        return fail_ctx(ctx, hip_fail(e, "assignment unpack kernel"));
     if (assign_out && ctx->gen &&
         (e = km::launch_gen_unpack(ctx->gen, ctx->dv, assign_out, ctx->stream)) != hipSuccess)
         return fail_ctx(ctx, hip_fail(e, "assignment unpack kernel"));
-    if (assign_out && !ctx->small && !ctx->incmm && !ctx->gen &&
+    if (assign_out && !ctx->small && !ctx->gen &&
         (e = hipMemcpyAsync(assign_out, ctx->dv.a, (size_t)ctx->n * sizeof(int32_t),
                             hipMemcpyDeviceToDevice, ctx->stream)) != hipSuccess)
         return fail_ctx(ctx, hip_fail(e, "hipMemcpyAsync assign"));
@@ -1300,8 +1264,10 @@ const char* kmeans_mti_path(const km_ctx* ctx) {
     if (!ctx) return "";
     if (ctx->small) return ctx->inc ? "stream-d16" : "stream-d16-full";
     if (ctx->large) return "global-mfma";
-    if (ctx->gen == km::kGenMat && ctx->k > 16 && ctx->k <= 128 && (ctx->d == 16 || ctx->d == 32)) return "lds-mfma";
-    if (ctx->incmm || ctx->gen == km::kGenMat) return "lds-inc";
+    if ((ctx->flags & KM_FLAG_STATS) && ctx->gen == km::kGenMat && ctx->k > 16 && ctx->k <= 128 &&
+        (ctx->d == 16 || ctx->d == 32))
+        return "lds-mfma";
+    if (ctx->gen == km::kGenMat) return "lds-inc";
     if (ctx->gen == km::kGenVec) return "lds-vector";
     if (ctx->variant % 16 == 8) return "lds-elkan";
     return ctx->variant % 16 ? "lds-mfma" : "lds-vector";

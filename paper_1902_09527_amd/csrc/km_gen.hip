@@ -1,6 +1,6 @@
-// Incremental MTI steps for any row width (km_gen.hip): the paper's skipping
-// of the data of the points Clause 1 keeps (section III-C) where the
-// specialised widths (16 and 32) do not apply.  Two kernels share the
+// Incremental MTI steps for any row width: the paper's skipping of the data
+// of the points Clause 1 keeps (section III-C: no row of such a point is
+// read) where the streaming path (d = 16, k <= 16) does not apply.  Two kernels share the
 // structure; which one runs is a rule on d and k (gen_kind):
 //   k_inc_vec  d <= 16 and few centroids: one lane per survivor, its row in
 //              registers, the MTI scan of the vector path (tighten, Clauses 2
@@ -427,13 +427,21 @@ __global__ __launch_bounds__(kGenThreads) void k_inc_vec(Dev P_, int first, int 
 // it spilled, 97 us a step against 64 us at 300K x 64, k = 50.  The general
 // kernel, which it replaces, took 1230 us there (43 us of the 64 are this
 // kernel's), 18.9 ms at 700K x 128, k = 56 (now 119 us a step) and 4.1 ms at
-// 575K x 174, k = 10 (now 250 us).
+// 575K x 174, k = 10 (now 250 us).  For d <= 32 a whole row is held and the
+// next batch's rows are the only loads ahead; up to k = 64 that leaves room for
+// three waves per SIMD: 20M x 32, k = 64 takes 0.79 ms a step, 1.10 at two
+// waves, and 1.21 took a form with bf16 operands, its centroids in registers
+// and queues by the blocks of centroids a survivor needs.  Leaving blocks of
+// centroids out by Clause 2 costs a tenth where few batches can (0.99 to 1.10
+// ms at two waves there): only the four-block form does (k > 64), where well
+// separated clusters leave out most of the products.
 
-template <int KB>
-constexpr int gen_mat_steps() { return KB >= 4 ? 2 : 4; }   // k-steps loaded ahead (kQS)
+// k-steps loaded ahead (kQS); ONE: all of a row (d <= 32).
+template <int KB, bool ONE>
+constexpr int gen_mat_steps() { return ONE || KB >= 4 ? 2 : 4; }
 
-template <int KB, bool VEC>
-__global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_inc_mat(Dev P_, int first, int nsub) {
+template <int KB, bool VEC, bool ONE>
+__global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_waves_per_eu(gen_mat_waves(KB, ONE) / 4))) void k_inc_mat(Dev P_, int first, int nsub) {
     const Dev P = with_scales(P_);
     IterState* st = P.st;
     if (st->done) {
@@ -442,7 +450,9 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) st->active = 1;
     constexpr int CB = KB == 8 ? 8 : 7;   // cluster bits of a state word
-    constexpr int QS = gen_mat_steps<KB>();
+    constexpr int QS = gen_mat_steps<KB, ONE>();
+    constexpr bool kSkip = KB == 4;       // Clause 2 per block of centroids
+    constexpr int NW = gen_mat_waves(KB, ONE), NT = 64 * NW;
     constexpr bool kTwo = KB <= 4;        // two k-steps at a time in an accumulator of their own
     const int k = P.k, d = P.d, tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -450,13 +460,15 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
     const int ns = (d + 15) / 16;
     const float xsc = st->xscale, xinv = st->xinv;
     const float ecmax = st->ec_max, ecs_max = st->ec_max * xsc, gamma = P.gamma;
-    const GenMatLds lay = gen_mat_lds(KB, d, k);
+    const GenMatLds lay = gen_mat_lds(KB, NW, d, k);
     const int AR = lay.ar;
     uint4* cau = reinterpret_cast<uint4*>(km_smem + lay.off_ca);   // [s][cb][hi, lo][lane]
     float* nb = reinterpret_cast<float*>(km_smem + lay.off_nb);
     float* thr = reinterpret_cast<float*>(km_smem + lay.off_thr);
     float* ecs = reinterpret_cast<float*>(km_smem + lay.off_ec);
     float* ddn = reinterpret_cast<float*>(km_smem + lay.off_ddn);
+    float* dup = reinterpret_cast<float*>(km_smem + lay.off_dup);
+    float* hm = reinterpret_cast<float*>(km_smem + lay.off_hm);
     uint64_t* acc = reinterpret_cast<uint64_t*>(km_smem + lay.off_acc);
     int* cnt = reinterpret_cast<int*>(km_smem + lay.off_cnt);
     int* tcount = reinterpret_cast<int*>(km_smem + lay.off_misc);
@@ -478,7 +490,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
         hi = make_uint4(h[0], h[1], h[2], h[3]);
         lo = make_uint4(o[0], o[1], o[2], o[3]);
     };
-    for (int i = tid; i < ns * KB * 64; i += kGenThreads) {
+    for (int i = tid; i < ns * KB * 64; i += NT) {
         const int l = i & 63, cb = (i >> 6) % KB, s = i / (64 * KB);
         const int j = cb * 32 + (l & 31), m0 = 16 * s + 8 * (l >> 5);
         float v[8];
@@ -490,14 +502,17 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
         cau[((s * KB + cb) * 2 + 1) * 64 + l] = lo;
     }
     // -|c|^2 / 2 in scaled units (padding centroids: a value no point reaches).
-    for (int i = tid; i < 32 * KB; i += kGenThreads) nb[i] = i < k ? -0.5f * ((P.cn2[i] * xsc) * xsc) : -0x1p100f;
-    for (int i = tid; i < k * AR; i += kGenThreads) acc[i] = 0;
-    for (int i = tid; i < k; i += kGenThreads) {
+    for (int i = tid; i < 32 * KB; i += NT) nb[i] = i < k ? -0.5f * ((P.cn2[i] * xsc) * xsc) : -0x1p100f;
+    for (int i = tid; i < k * AR; i += NT) acc[i] = 0;
+    for (int i = tid; i < k; i += NT) {
         thr[i] = first ? 0.f : clause1_thr(P.s[i], P.dhi[i]);
         ecs[i] = P.ec[i];
         ddn[i] = P.ddnf[i];
+        if constexpr (kSkip) dup[i] = P.dupf[i];
         cnt[i] = 0;
     }
+    if constexpr (kSkip)
+        for (int i = tid; i < 4 * k; i += NT) hm[i] = P.hm[i];
     if (tid < kNumStat) bst[tid] = 0;
     if (tid == 0) *tcount = 0;
     __syncthreads();
@@ -737,15 +752,32 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
         const bool live = col < bcnt;
         const int inc = first ? -1 : state_cluster<CB>(bw);
         const float* rp = P.X + (int64_t)bp * d;
+        // Clause 2 per block of centroids over the whole batch: a block is
+        // left out when every survivor's bound is at most half the distance
+        // from its centroid to each of the block's (its own block never is).
+        bool eval[KB];
+        int nreal = k;   // centroids of the blocks taken
+#pragma unroll
+        for (int cb = 0; cb < KB; ++cb) eval[cb] = true;
+        if constexpr (kSkip) {
+            if (!first) {
+                const float u = (state_value<CB>(bw) + dup[inc]) * kUp;
+#pragma unroll
+                for (int cb = 0; cb < KB; ++cb) {
+                    eval[cb] = __ballot(live && !(u <= hm[4 * inc + cb])) != 0;
+                    if (!eval[cb]) nreal -= min(32, max(k - 32 * cb, 0));
+                }
+            }
+        }
         f32x16 dot[KB];
 #pragma unroll
         for (int cb = 0; cb < KB; ++cb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) dot[cb][e] = 0.f;
+            for (int e = 0; e < 16; ++e) dot[cb][e] = eval[cb] ? 0.f : -INFINITY;
         float x2 = 0.f;
-        for (int s0 = 0; s0 < ns; s0 += QS) {
+        for (int s0 = 0; s0 < (ONE ? 1 : ns); s0 += QS) {
             Ahead N;
-            const bool more = s0 + QS < ns;
+            const bool more = !ONE && s0 + QS < ns;
             if (more) load_steps(rp, s0 + QS, N);
 #pragma unroll
             for (int i = 0; i < QS; i += 2) {
@@ -772,6 +804,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
                 const uint4* ca = cau + (s0 + i) * KB * 128 + lane;
 #pragma unroll
                 for (int cb = 0; cb < KB; ++cb) {
+                    if (!eval[cb]) continue;   // uniform
                     f32x16 pr = kTwo ? f32x16{} : dot[cb];
                     const uint4 ah = ca[cb * 128], al = ca[cb * 128 + 64];
                     pr = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf(ah), bf(blo[0]), pr, 0, 0, 0);
@@ -841,7 +874,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
             moved = b != inc;
             my_changed += moved ? 1u : 0u;
         }
-        if (live && half == 0) my_comp += (uint32_t)k;
+        if (live && half == 0) my_comp += (uint32_t)nreal;
         const uint64_t lm = __ballot(live && several && half == 0);
         if (lm) {   // list them with their candidates
             const int e = ln + __popcll(lm & ((1ull << col) - 1ull));
@@ -934,7 +967,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
             if (++sub == nsub) {
                 sub = 0;
                 int nxt = 0;
-                if (lane == 0) nxt = wt_lo + kGenWaves + atomicAdd(tcount, 1);
+                if (lane == 0) nxt = wt_lo + NW + atomicAdd(tcount, 1);
                 wt = __builtin_amdgcn_readfirstlane(nxt);
             }
             continue;
@@ -960,7 +993,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
         atomicAdd(bs + kStRecheck, (unsigned long long)v3);
     }
     __syncthreads();
-    flush_block(P, acc, cnt, bst, AR, kGenThreads);
+    flush_block(P, acc, cnt, bst, AR, NT);
 }
 
 template <int CB>
@@ -981,19 +1014,26 @@ __global__ __launch_bounds__(256) void k_gen_unpack(const uint32_t* __restrict__
 // counts distances exactly as the MTI scan does, one centroid after another.
 static int gen_mat_kb(int k) { return k <= 32 ? 1 : k <= 64 ? 2 : k <= 128 ? 4 : 8; }
 
+int gen_waves(GenKind kind, int d, int k) { return kind == kGenMat ? gen_mat_waves(gen_mat_kb(k), d <= 32) : kGenWaves; }
+
 GenKind gen_kind(int64_t n, int d, int k, int max_lds) {
     if (n > (int64_t)INT_MAX - kGenTile) return kGenNone;   // int32 point indices, also over the padding
     if (d <= kGenVecMaxD && k <= kGenVecMaxK && k * ((d + 3) / 4 * 4) <= kGenVecMaxKD &&
         gen_vec_lds((d + 3) / 4 * 4, d, k).bytes <= max_lds)
         return kGenVec;
-    if (k <= kGenMatMaxK && d <= kGenMatMaxD && gen_mat_lds(gen_mat_kb(k), d, k).bytes <= max_lds) return kGenMat;
+    if (k <= kGenMatMaxK && d <= kGenMatMaxD && gen_mat_lds(gen_mat_kb(k), gen_waves(kGenMat, d, k), d, k).bytes <= max_lds) return kGenMat;
     return kGenNone;
 }
 
 int gen_lds_bytes(GenKind kind, int d, int k) {
-    return kind == kGenVec ? gen_vec_lds((d + 3) / 4 * 4, d, k).bytes : gen_mat_lds(gen_mat_kb(k), d, k).bytes;
+    return kind == kGenVec ? gen_vec_lds((d + 3) / 4 * 4, d, k).bytes : gen_mat_lds(gen_mat_kb(k), gen_waves(kGenMat, d, k), d, k).bytes;
 }
 
+#define KM_GEN_KB(MATX, V_, O_)                                             \
+    {                                                                       \
+        if (kb == 1) MATX(1, V_, O_) else if (kb == 2) MATX(2, V_, O_)      \
+        else if (kb == 4) MATX(4, V_, O_) else MATX(8, V_, O_)              \
+    }
 #define KM_GEN_CASES(VECX, MATX)                                            \
     if (kind == kGenVec) {                                                  \
         const int dp = (dv.d + 3) / 4 * 4;                                  \
@@ -1002,17 +1042,15 @@ int gen_lds_bytes(GenKind kind, int d, int k) {
         const int kb = gen_mat_kb(dv.k);                                    \
         const bool vec = dv.d % 4 == 0 && reinterpret_cast<uintptr_t>(dv.X) % 16 == 0; \
         if (vec) {                                                          \
-            if (kb == 1) MATX(1, true) else if (kb == 2) MATX(2, true)      \
-            else if (kb == 4) MATX(4, true) else MATX(8, true)              \
+            if (dv.d <= 32) KM_GEN_KB(MATX, true, true) else KM_GEN_KB(MATX, true, false)    \
         } else {                                                            \
-            if (kb == 1) MATX(1, false) else if (kb == 2) MATX(2, false)    \
-            else if (kb == 4) MATX(4, false) else MATX(8, false)            \
+            if (dv.d <= 32) KM_GEN_KB(MATX, false, true) else KM_GEN_KB(MATX, false, false)  \
         }                                                                   \
     }
 
 const void* gen_symbol(GenKind kind, const Dev& dv) {
 #define KM_V(DP_) return reinterpret_cast<const void*>(&k_inc_vec<DP_>);
-#define KM_M(KB_, V_) return reinterpret_cast<const void*>(&k_inc_mat<KB_, V_>);
+#define KM_M(KB_, V_, O_) return reinterpret_cast<const void*>(&k_inc_mat<KB_, V_, O_>);
     KM_GEN_CASES(KM_V, KM_M)
 #undef KM_V
 #undef KM_M
@@ -1020,7 +1058,7 @@ const void* gen_symbol(GenKind kind, const Dev& dv) {
 
 hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, int first, hipStream_t s) {
 #define KM_V(DP_) { hipLaunchKernelGGL(k_inc_vec<DP_>, dim3(grid), dim3(kGenThreads), lds_bytes, s, dv, first, nsub); }
-#define KM_M(KB_, V_) { hipLaunchKernelGGL((k_inc_mat<KB_, V_>), dim3(grid), dim3(kGenThreads), lds_bytes, s, dv, first, nsub); }
+#define KM_M(KB_, V_, O_) { hipLaunchKernelGGL((k_inc_mat<KB_, V_, O_>), dim3(grid), dim3(64 * gen_mat_waves(KB_, O_)), lds_bytes, s, dv, first, nsub); }
     KM_GEN_CASES(KM_V, KM_M)
 #undef KM_V
 #undef KM_M

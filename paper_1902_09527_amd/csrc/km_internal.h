@@ -74,7 +74,7 @@ struct Dev {
     float* ddnf;          // incremental path: k cumulative drifts, rounded down to float32 (else null)
     uint32_t* w;          // incremental path: point states (cluster and bound, below), padded
     uint64_t* sums;       // incremental path: k*d + k exact sums and counts, carried across steps (else null)
-    float* hm;            // incremental path: k x 4, min over centroid block cb of h[a][j] (h[a][a] = 0), else null
+    float* hm;            // incremental path, 64 < k <= 128: k x 4, min over centroid block cb of h[a][j] (h[a][a] = 0), else null
     uint64_t* rows;       // general incremental path: kGenRows x L accumulation rows (zero between steps), else null
     int64_t* iterm;       // inertia (general incremental and global paths): 2 k fixed-point terms of the step (k_update), else null
     const double* x2sum;  // sum of all |x|^2 (set-up), as an unevaluated sum of two doubles, else null
@@ -453,66 +453,6 @@ int assign_variant(int d, int k, bool aligned, bool vector_only, bool elkan);
 const void* assign_kernel_symbol(int variant);
 
 
-// Incremental matrix-core step (km_incmm.hip), d = 16 or 32, k <= 128: the
-// point states are streamed (4 bytes per point), only the Clause-1
-// survivors' rows are gathered, and the sums move the rows of the points
-// whose cluster changed (the running sums are carried in Dev::sums).
-// Point state: bits 6..0 the cluster, the word with those bits cleared a
-// float32 value v (rounded up) with v + D_a an upper bound on the point's
-// distance to its centroid, D_a the cumulative drift of its cluster.
-constexpr int kIMWaves = 8;          // waves per block
-constexpr int kIMBatch = 32;         // survivors per matrix-core batch
-constexpr int kIMSub = 64;           // points per Clause-1 sub-step of a wave (one per lane)
-constexpr int kIMTile = 4 * kIMSub;  // points a wave takes at once; the state array is padded to it
-constexpr int kIMQcap = kIMBatch + kIMSub;   // entries of one survivor queue
-constexpr int kIMMaxK = 128;
-
-// Survivor queues of a wave: one per set of 32-centroid blocks a survivor
-// needs (KB <= 2: 1 or 3 sets), or one per block of its cluster (KB = 4).
-__host__ __device__ constexpr int inc_mm_queues(int KB) { return KB == 4 ? 4 : (1 << KB) - 1; }
-
-struct IncMMLds {
-    int off_c, off_ca, off_cn, off_thr, off_ec, off_ddn, off_dup, off_hm, off_nb, off_acc, off_cnt, off_misc, off_q,
-        off_x, bytes;
-};
-
-// Every offset depends on D and KB only (constants of each kernel variant).
-__host__ __device__ inline IncMMLds inc_mm_lds(int D, int KB) {
-    IncMMLds L;
-    int o = 0;
-    auto take = [&](int bytes) {
-        o = (o + 15) / 16 * 16;
-        int r = o;
-        o += bytes;
-        return r;
-    };
-    const int kp = 32 * KB;
-    L.off_c = take(4 * kp * D);                          // float32 centroid rows
-    L.off_ca = take(KB == 4 ? 4 * KB * (D / 2) * 64 : 0); // matrix-core operands (KB = 4)
-    L.off_cn = take(4 * kp);                             // squared centroid norms
-    L.off_thr = take(4 * kIMMaxK);                       // Clause-1 thresholds
-    L.off_ec = take(4 * kIMMaxK);
-    L.off_ddn = take(4 * kIMMaxK);
-    L.off_dup = take(4 * kIMMaxK);
-    L.off_hm = take(4 * kIMMaxK * 4);                    // min half-distance from a cluster to each block
-    L.off_nb = take(4 * kp);                             // -|c|^2 / 2 of each centroid (-huge for padding)
-    L.off_acc = take(8 * kp * (D + 1));                  // fixed-point sums of the moves (rows of D + 1)
-    L.off_cnt = take(4 * kp);
-    L.off_misc = take(64);                               // tile counter at 0, kNumStat uint64 counters at 16
-    L.off_q = take(kIMWaves * 2 * inc_mm_queues(KB) * kIMQcap * 4);   // per wave: queues of (point, state)
-    L.off_x = take(kIMWaves * kIMBatch * (D + 4) * 4);   // per wave: the batch's rows (+ 4 spare words)
-    L.bytes = (o + 15) / 16 * 16;
-    return L;
-}
-
-bool inc_mm_applies(int64_t n, int d, int k, bool aligned);
-int inc_mm_kb(int k);
-const void* inc_mm_symbol(int d, int k);
-// One step (first: no bounds yet, every point is scanned).
-hipError_t launch_inc_mm(const Dev& dv, int grid, int lds_bytes, int first, hipStream_t s);
-// assign_out[i] = cluster of point i from the point states.
-hipError_t launch_inc_mm_unpack(const Dev& dv, int32_t* assign_out, hipStream_t s);
-
 // General incremental steps (km_gen.hip): any d, the widths and cluster
 // counts for which the tables, the exact sums and the waves' lists fit in LDS.
 constexpr int kGenWaves = 8;          // waves per block
@@ -521,6 +461,7 @@ constexpr int kGenTile = 256;         // most points a wave takes at once (64, 1
 constexpr int kGenRows = 16;          // accumulation rows
 constexpr int kGenVecMaxD = 16, kGenVecMaxK = 64, kGenVecMaxKD = 256;   // one lane per survivor up to here
 constexpr int kGenVecQ = 128;         // survivor queue of a wave: one batch of 64 and one sub-step of 64 points
+constexpr int kTabMinK = 128;          // the centroid table forms hm up to this k (64 < k: the form with four blocks)
 constexpr int kGenMatMaxK = 256, kGenMatMaxD = 1024;
 
 enum GenKind { kGenNone = 0, kGenVec = 1, kGenMat = 2 };
@@ -567,9 +508,12 @@ struct GenMatWave {
     uint16_t pl[kGenPairs + 32 * kGenCand];        // the pairs: listed survivor << 8 | centroid
 };
 struct GenMatLds {
-    int off_ca, off_nb, off_thr, off_ec, off_ddn, off_acc, off_cnt, off_misc, off_w, ar, bytes;
+    int off_ca, off_nb, off_thr, off_ec, off_ddn, off_dup, off_hm, off_acc, off_cnt, off_misc, off_w, ar, bytes;
 };
-__host__ __device__ inline GenMatLds gen_mat_lds(int KB, int d, int k) {
+// Waves per block of the matrix-core form: three per SIMD where its registers
+// allow it (k <= 64 and whole rows of d <= 32 held: 168 of them), else two.
+__host__ __device__ constexpr int gen_mat_waves(int KB, bool one) { return one && KB <= 2 ? 12 : 8; }
+__host__ __device__ inline GenMatLds gen_mat_lds(int KB, int waves, int d, int k) {
     GenMatLds L;
     int o = 0;
     auto take = [&](int bytes) {
@@ -584,10 +528,13 @@ __host__ __device__ inline GenMatLds gen_mat_lds(int KB, int d, int k) {
     L.off_thr = take(4 * k);
     L.off_ec = take(4 * k);
     L.off_ddn = take(4 * k);
+    const bool skip = KB == 4;              // Clause 2 per block of centroids
+    L.off_dup = take(skip ? 4 * k : 0);
+    L.off_hm = take(skip ? 16 * k : 0);     // min half-distance from a cluster to each block
     L.off_acc = take(8 * k * L.ar);
     L.off_cnt = take(4 * k);
     L.off_misc = take(64);
-    L.off_w = take(kGenWaves * (int)sizeof(GenMatWave));
+    L.off_w = take(waves * (int)sizeof(GenMatWave));
     L.bytes = (o + 15) / 16 * 16;
     return L;
 }
@@ -595,6 +542,7 @@ __host__ __device__ inline GenMatLds gen_mat_lds(int KB, int d, int k) {
 // Which form takes (n, d, k), if any; its LDS bytes, symbol and launch.
 GenKind gen_kind(int64_t n, int d, int k, int max_lds);
 int gen_lds_bytes(GenKind kind, int d, int k);
+int gen_waves(GenKind kind, int d, int k);   // waves per block
 const void* gen_symbol(GenKind kind, const Dev& dv);
 hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, int first, hipStream_t s);
 hipError_t launch_gen_unpack(GenKind kind, const Dev& dv, int32_t* assign_out, hipStream_t s);

@@ -333,7 +333,7 @@ __global__ __launch_bounds__(256) void k_centroid_table(Dev P, int force) {
     const int i = blockIdx.x, k = P.k, d = P.d, tid = threadIdx.x, lane = tid & 63;
     if (P.iterm && !force && i == 0 && tid < 64) close_inertia(P);
     const double* ci = P.C64 + (int64_t)i * d;
-    __shared__ float hrow[kIMMaxK], red[4], redm[4];
+    __shared__ float hrow[kTabMinK], red[4], redm[4];
     const int G = d <= 4 ? 1 : d <= 8 ? 2 : d <= 16 ? 4 : d <= 32 ? 8 : 16;
     const int g = tid & (G - 1);
     float mn = INFINITY;
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(256) void k_centroid_table(Dev P, int force) {
         for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
         if (lane == 0) P.cn2[i] = (float)n2;
     } else if (tid < 192) {
-        if (P.hm) {   // incremental path (k <= 128): min of row i over each 32-centroid block (h[i][i] = 0)
+        if (P.hm) {   // incremental path (64 < k <= 128): min of row i over each 32-centroid block (h[i][i] = 0)
             const int j = tid - 64;
             float m = j < k ? hrow[j] : INFINITY;
 #pragma unroll
