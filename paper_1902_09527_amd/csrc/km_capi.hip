@@ -342,10 +342,12 @@ int enqueue_iteration(km_ctx* c) {
                    : km::launch_reduce(c->dv, c->stream);
     if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "reduce kernel"));
     if ((e = mark(2)) != hipSuccess) return fail_ctx(c, hip_fail(e, "hipEventRecord"));
-    if ((e = km::launch_update(c->dv, c->stream)) != hipSuccess)
+    const bool one = c->gen && km::gen_finish_applies(c->d, c->k);   // update and table in one launch
+    if ((e = one ? km::launch_gen_finish(c->dv, c->stream) : km::launch_update(c->dv, c->stream)) != hipSuccess)
         return fail_ctx(c, hip_fail(e, "update kernel"));
     if ((e = mark(3)) != hipSuccess) return fail_ctx(c, hip_fail(e, "hipEventRecord"));
-    e = c->large ? km::launch_large_table(c->dv, c->lg, 0, c->stream)
+    e = one        ? hipSuccess
+        : c->large ? km::launch_large_table(c->dv, c->lg, 0, c->stream)
                  : km::launch_centroid_table(c->dv, 0, c->stream);
     if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "centroid table kernel"));
     if ((e = mark(4)) != hipSuccess) return fail_ctx(c, hip_fail(e, "hipEventRecord"));

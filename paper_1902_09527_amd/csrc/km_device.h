@@ -207,6 +207,52 @@ __device__ __forceinline__ DD dd_wave_sum(DD a) {
     return a;
 }
 
+// The end of a step's bookkeeping (one thread): its counters sc into the
+// history and the totals, the step count, the stop test and the progress
+// word.
+__device__ inline void close_step(const Dev& P, const uint64_t* sc, double inertia) {
+    IterState* st = P.st;
+    const int t = st->t;
+    IterRec& r = P.rec[t % kHistCap];
+    r.changed = (int64_t)sc[kStChanged];
+    r.computed = (int64_t)sc[kStComputed];
+    r.clause1 = (int64_t)sc[kStClause1];
+    r.rechecks = (int64_t)sc[kStRecheck];
+    r.inertia = inertia;
+    st->changed_last = r.changed;
+    st->tot_computed += r.computed;
+    st->tot_clause1 += r.clause1;
+    st->tot_rechecks += r.rechecks;
+    st->inertia_last = inertia;
+    st->t = t + 1;
+    const bool tol_hit = (double)r.changed < st->tol_n;
+    const bool done = tol_hit || t + 1 >= st->max_iters;
+    if (done) {
+        st->done = 1;
+        st->converged = tol_hit ? 1 : 0;
+    }
+    report_step(st, t, done);
+}
+
+// A cluster's inertia term c (n c - 2 S) of one coordinate: c the centroid
+// the step used, n the member count, S = q 2^-S the exact sum.
+__device__ __forceinline__ DD inertia_add(DD term, double c, uint64_t n, int64_t q, double qinv) {
+    const DD S = dd_int(q);
+    const double nc = (double)n * c;
+    term = dd_fma(term, c, nc);
+    term = dd_fma(term, c, fma((double)n, c, -nc));
+    term = dd_fma(term, c, -2.0 * qinv * S.h);
+    return dd_fma(term, c, -2.0 * qinv * S.l);
+}
+
+// A cluster's whole term as fixed point, 2^SI (h + l 2^-40).
+__device__ __forceinline__ void inertia_fixed(DD term, double iscale, int64_t* out) {
+    const double t = term.h * iscale, h = floor(t);
+    const DD rest = dd_add(DD{t - h, 0.0}, term.l * iscale);
+    out[0] = (int64_t)h;
+    out[1] = (int64_t)rint((rest.h + rest.l) * 0x1p40);
+}
+
 // The inertia of the step that has just ended, by the first wave of a block:
 // sum |x|^2 + sum_j (n_j |c_j|^2 - 2 c_j . S_j), the cluster terms as the
 // fixed-point integers k_update left (their sum does not depend on the

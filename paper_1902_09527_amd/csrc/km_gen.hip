@@ -996,6 +996,198 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
     flush_block(P, acc, cnt, bst, AR, NT);
 }
 
+// ---------------------------------------------------------------------------
+// The end of a step in one block: new centroids, drift, bookkeeping and the
+// half-distance table, as k_update and k_centroid_table form them, from the
+// accumulation rows.  Those two are launches of k blocks, latency each (8.2
+// and 4.2 us at k = 8, d = 5, with the gaps 13 to 17 us between two steps of
+// k_inc_vec); here the new centroids stay in LDS between the phases (6.2 us; a run of 15 steps
+// of 10K x 5, k = 8 takes 311 us, 420 before; 1M x 32, k = 20 1238 us, 1264).
+// One block does all the work, so only while that is little (gen_finish_applies).
+
+constexpr int kFinThreads = 512;
+
+__global__ __launch_bounds__(kFinThreads) void k_gen_finish(Dev P_) {
+    const Dev P = with_scales(P_);
+    IterState* st = P.st;
+    const int k = P.k, d = P.d, kd = k * d, tid = threadIdx.x, lane = tid & 63;
+    double* cn = reinterpret_cast<double*>(km_smem);        // [k][DS] new centroids
+    const int DS = d | 1;
+    double* co = cn + k * DS;                               // [k][DS] the step's centroids
+    int64_t* qs = reinterpret_cast<int64_t*>(co + k * DS);  // [k][DS] exact sums (the magic offset removed)
+    uint64_t* nc = reinterpret_cast<uint64_t*>(qs + k * DS);   // [k] member counts
+    uint64_t* sc = nc + k;                                  // [8] the step's counters
+    float* ecs = reinterpret_cast<float*>(sc + 8);          // [k]
+    auto row_sum = [&](int64_t o) __attribute__((always_inline)) {
+        uint64_t v = 0;
+#pragma unroll
+        for (int r = 0; r < kGenRows; ++r) v += P.rows[(int64_t)r * P.L + o];
+        return v;
+    };
+    auto clear = [&](int64_t o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < kGenRows; ++r) P.rows[(int64_t)r * P.L + o] = 0;
+    };
+    // Requested before the loop state is looked at: one trip to memory.
+    const int e0 = min(tid, kd - 1), a0 = min(tid, k + kNumStat - 1);
+    uint64_t tv0 = P.sums[e0] + row_sum(e0);
+    const double cold0 = P.C64[e0];
+    const uint64_t cv0 = row_sum(kd + a0) + (a0 < k ? P.sums[kd + a0] : 0);
+    if (!st->active) return;
+    for (int i = tid; i < k + kNumStat; i += kFinThreads) {   // counts, then the counters
+        const uint64_t v = i == tid ? cv0 : row_sum(kd + i) + (i < k ? P.sums[kd + i] : 0);
+        if (i < k) {
+            nc[i] = v;
+            P.sums[kd + i] = v;
+        } else {
+            sc[i - k] = v;
+        }
+        clear(kd + i);
+    }
+    __syncthreads();
+    for (int e = tid; e < kd; e += kFinThreads) {
+        const int j = e / d, m = e - j * d;
+        const uint64_t tv = e == tid ? tv0 : P.sums[e] + row_sum(e);
+        const double cold = e == tid ? cold0 : P.C64[e];
+        const uint64_t n = nc[j];
+        const int64_t q = (int64_t)(tv - n * kMagicBits);
+        co[j * DS + m] = cold;
+        qs[j * DS + m] = q;
+        cn[j * DS + m] = n ? ((double)q * P.qinv) / (double)n : cold;
+        P.sums[e] = tv;
+        clear(e);
+    }
+    __syncthreads();
+    // Per cluster, a group of 8 lanes: projection (spherical), drift, float32
+    // copy, its rounding error and norm, the inertia term.
+    const int g8 = tid & 7;
+    for (int j0 = 0; j0 < k; j0 += kFinThreads / 8) {   // whole groups take every round
+        const int j = min(j0 + tid / 8, k - 1);
+        const uint64_t n = nc[j];
+        double* c = cn + j * DS;
+        const double* o = co + j * DS;
+        auto sum8 = [&](double v) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 1; s < 8; s <<= 1) v += __shfl_xor(v, s);
+            return v;
+        };
+        double scale = 1.0;
+        bool keep = n == 0;
+        if (P.flags & KM_FLAG_SPHERICAL) {
+            double s = 0.0;
+            for (int m = g8; m < d; m += 8) s = fma(c[m], c[m], s);
+            s = sum8(s);
+            if (n > 0 && s > 0.0) scale = sqrt(s);
+            else keep = true;
+        }
+        const bool mine = j0 + tid / 8 < k;   // the group's own cluster (not the repeated last)
+        double dr = 0.0, de = 0.0, n2 = 0.0;
+        DD term{};
+        for (int m = g8; m < d; m += 8) {
+            const double cold = o[m], cnew = keep ? cold : c[m] / scale;
+            if (P.iterm) term = inertia_add(term, cold, n, qs[j * DS + m], P.qinv);
+            const float c32 = (float)cnew;
+            const double df = cnew - cold, e = (double)c32 - cnew;
+            dr = fma(df, df, dr);
+            de = fma(e, e, de);
+            n2 = fma((double)c32, (double)c32, n2);
+            if (mine) {
+                c[m] = cnew;
+                P.C64[j * d + m] = cnew;
+                P.C32[j * d + m] = c32;
+            }
+        }
+        dr = sum8(dr);
+        de = sum8(de);
+        n2 = sum8(n2);
+        if (P.iterm) {
+#pragma unroll
+            for (int s = 1; s < 8; s <<= 1) term = dd_add(term, DD{__shfl_xor(term.h, s), __shfl_xor(term.l, s)});
+        }
+        if (mine && g8 == 0) {
+            const double fd = sqrt(dr);
+            const float ec = f32_up(sqrt(de) * (1.0 + 0x1p-40));
+            const double hi = (P.dhi[j] + fd * (1.0 + 0x1p-40)) * (1.0 + 0x1p-50);
+            const double lo = (P.dlo[j] + fd * (1.0 - 0x1p-40)) * (1.0 - 0x1p-50);
+            P.f[j] = f32_up(fd * (1.0 + 0x1p-40));
+            P.ec[j] = ec;
+            ecs[j] = ec;
+            P.cn2[j] = (float)n2;
+            P.dhi[j] = hi;
+            P.dlo[j] = lo;
+            P.dupf[j] = f32_up(hi);
+            P.ddnf[j] = f32_down(lo);
+            if (P.iterm) inertia_fixed(term, P.iscale, P.iterm + 2 * j);
+        }
+    }
+    __syncthreads();
+    // The table, 16 lanes per row: h (k_inc_vec reads it), s, and the minima
+    // over each 32 centroids.
+    const int g16 = tid & 15;
+    for (int i0 = 0; i0 < k; i0 += kFinThreads / 16) {
+        const int i = min(i0 + tid / 16, k - 1);
+        const double* ci = cn + i * DS;
+        float mn = INFINITY, bm[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
+        for (int j = g16; j < k; j += 16) {
+            const double* cj = cn + j * DS;
+            double a = 0.0;
+            for (int m = 0; m < d; ++m) {
+                const double t = ci[m] - cj[m];
+                a = fma(t, t, a);
+            }
+            const float hv = j == i ? 0.f : f32_down(0.5 * sqrt(a) * (1.0 - 0x1p-40));
+            if (j != i) mn = fminf(mn, hv);
+            if (P.hm) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (j >> 5 == b) bm[b] = fminf(bm[b], hv);
+            }
+            P.h[i * k + j] = hv;
+        }
+#pragma unroll
+        for (int s = 1; s < 16; s <<= 1) {
+            mn = fminf(mn, __shfl_xor(mn, s));
+            if (P.hm) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) bm[b] = fminf(bm[b], __shfl_xor(bm[b], s));
+            }
+        }
+        if (g16 == 0) {
+            P.s[i] = mn;
+            if (P.hm) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) P.hm[4 * i + b] = bm[b];
+            }
+        }
+    }
+    if (tid < 64) {   // the bookkeeping
+        float em = 0.f;
+        for (int j = lane; j < k; j += 64) em = fmaxf(em, ecs[j]);
+#pragma unroll
+        for (int s = 32; s > 0; s >>= 1) em = fmaxf(em, __shfl_xor(em, s));
+        if (lane == 0) {
+            st->ec_max = em;
+            close_step(P, sc, NAN);
+        }
+        if (P.iterm) {
+            __threadfence_block();
+            close_inertia(P);
+        }
+    }
+}
+
+static int gen_finish_lds(int d, int k) { return k * (d | 1) * 24 + k * 12 + 64 + 16; }
+
+bool gen_finish_applies(int d, int k) {
+    // one block: 18 words read per coordinate, k^2 d differences
+    return k * d <= 1024 && k * k * d <= 65536;
+}
+
+hipError_t launch_gen_finish(const Dev& dv, hipStream_t s) {
+    hipLaunchKernelGGL(k_gen_finish, dim3(1), dim3(kFinThreads), gen_finish_lds(dv.d, dv.k), s, dv);
+    return hipGetLastError();
+}
+
 template <int CB>
 __global__ __launch_bounds__(256) void k_gen_unpack(const uint32_t* __restrict__ w, int64_t n, int32_t* __restrict__ a) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;

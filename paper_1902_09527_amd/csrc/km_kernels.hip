@@ -1341,14 +1341,7 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
         const double cnew = keep ? cold : mean(tv) / scale;
         if (P.sums) P.sums[o] = tv;
         clear(o);
-        if (P.iterm) {   // c (n c - 2 S)
-            const DD S = dd_int((int64_t)(tv - count * kMagicBits));
-            const double nc = (double)count * cold;
-            term = dd_fma(term, cold, nc);
-            term = dd_fma(term, cold, fma((double)count, cold, -nc));
-            term = dd_fma(term, cold, -2.0 * P.qinv * S.h);
-            term = dd_fma(term, cold, -2.0 * P.qinv * S.l);
-        }
+        if (P.iterm) term = inertia_add(term, cold, count, (int64_t)(tv - count * kMagicBits), P.qinv);
         const double df = cnew - cold;
         dr = fma(df, df, dr);
         const float c32 = (float)cnew;
@@ -1364,13 +1357,7 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
     }
     if (P.iterm) {
         term = dd_wave_sum(term);
-        if (threadIdx.x == 0) {   // as 2^SI (h + l 2^-40), l in [0, 2^40)
-            const double t = term.h * P.iscale;
-            const double h = floor(t);
-            const DD rest = dd_add(DD{t - h, 0.0}, term.l * P.iscale);
-            P.iterm[2 * j] = (int64_t)h;
-            P.iterm[2 * j + 1] = (int64_t)rint((rest.h + rest.l) * 0x1p40);
-        }
+        if (threadIdx.x == 0) inertia_fixed(term, P.iscale, P.iterm + 2 * j);
     }
     if (threadIdx.x == 0) {
         P.f[j] = f32_up(sqrt(dr) * (1.0 + 0x1p-40));
@@ -1397,33 +1384,9 @@ __global__ __launch_bounds__(64) void k_update(Dev P_) {
     }
     if (j == 0 && threadIdx.x == 0) {
         uint64_t* sc = P.rows ? tot : P.total + (int64_t)k * d + k;
-        const int64_t changed = (int64_t)sc[kStChanged];
-        const int64_t computed = (int64_t)sc[kStComputed];
-        const int64_t c1 = (int64_t)sc[kStClause1];
-        const int64_t rc = (int64_t)sc[kStRecheck];
-        const int64_t iq = (int64_t)sc[kStInertia];
+        const bool full_read = (P.flags & KM_FLAG_STATS) && !P.iterm;   // with iterm close_inertia writes it
+        close_step(P, sc, full_read ? (double)(int64_t)sc[kStInertia] * P.iinv : NAN);
         for (int c = 0; c < kNumStat; ++c) sc[c] = 0;
-        // with iterm written by the centroid table (close_inertia)
-        const double inertia = (P.flags & KM_FLAG_STATS) && !P.iterm ? (double)iq * P.iinv : NAN;
-        const int t = st->t;
-        IterRec& r = P.rec[t % kHistCap];
-        r.changed = changed;
-        r.computed = computed;
-        r.clause1 = c1;
-        r.rechecks = rc;
-        r.inertia = inertia;
-        st->changed_last = changed;
-        st->tot_computed += computed;
-        st->tot_clause1 += c1;
-        st->tot_rechecks += rc;
-        st->inertia_last = inertia;
-        st->t = t + 1;
-        const bool tol_hit = (double)changed < st->tol_n;
-        if (tol_hit || t + 1 >= st->max_iters) {
-            st->done = 1;
-            st->converged = tol_hit ? 1 : 0;
-        }
-        report_step(st, t, tol_hit || t + 1 >= st->max_iters);
     }
 }
 
