@@ -1115,6 +1115,7 @@ static int pp_seed_impl(const float* X, int64_t n, int32_t d, int32_t k, const d
     P.Mb = reinterpret_cast<uint64_t*>(ws + L.mb);
     P.dcc = reinterpret_cast<double*>(ws + L.dcc);
     P.cnt = stats ? reinterpret_cast<uint64_t*>(ws + L.cnt) : nullptr;
+    P.done = stats ? nullptr : reinterpret_cast<uint32_t*>(ws + L.cnt);   // the counters' words are free without stats
     P.G = (int32_t)((n + km::kPPChunk - 1) / km::kPPChunk);
     P.L = ceil_log2_u64((uint64_t)n);
     P.prune = (flags & KM_PP_NO_PRUNE) ? 0 : 1;

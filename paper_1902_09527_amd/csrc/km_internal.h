@@ -567,6 +567,7 @@ struct PPArgs {
     uint64_t* Mb;         // k: bits of max D2 after the pass with seed t
     double* dcc;          // k: lower bounds of ||c_a - c_new||^2 (pruning only)
     uint64_t* cnt;        // 2k: distances computed and rows improved per pass, or null
+    uint32_t* done;       // blocks that have formed their weight sum (weights and draw in one launch), or null
     int32_t G;            // chunks = ceil(n / kPPChunk)
     int32_t L;            // smallest L with n <= 2^L
     int32_t prune;        // 1: triangle-inequality skip test

@@ -22,6 +22,7 @@
 //                the maximum the pass before it left in its slot;
 //   k_pp_select  one workgroup: scans the block sums, finds the block and
 //                then the point of the draw, writes the seed index and row;
+//   k_pp_draw    both of these in one launch, where nothing is counted;
 //   k_pp_dcc     the distances from the new seed to the earlier seeds (the
 //                pruning table of the next pass), spread over the chip.
 #include <math.h>
@@ -272,10 +273,138 @@ __global__ __launch_bounds__(kPPThreads) void k_pp_weights(PPArgs P, int t) {
     }
 }
 
+// The new seed (row pick) written as seed t + 1, and, with table, the
+// seed-to-seed table of its pass (one thread per earlier seed; as in k_pp_dcc).
+// Every thread of the block calls it with the same pick.
+__device__ __forceinline__ void put_seed(const PPArgs& P, int t, int64_t pick, int table) {
+    const int d = P.d;
+    if (threadIdx.x == 0) P.idx[t + 1] = pick;
+    const float* __restrict__ xp = P.X + pick * d;
+    for (int m = threadIdx.x; m < d; m += blockDim.x) P.C[(int64_t)(t + 1) * d + m] = xp[m];
+    if (!table) return;
+    for (int a = threadIdx.x; a <= t; a += blockDim.x) {
+        const float* __restrict__ ca = P.C + (int64_t)a * d;
+        double acc = 0.0;
+#pragma unroll 8
+        for (int m = 0; m < d; ++m) {
+            const double e = (double)ca[m] - (double)xp[m];
+            acc = fma(e, e, acc);
+        }
+        P.dcc[a] = acc * (1.0 - 0x1p-28);
+    }
+}
+
+// k_pp_weights and k_pp_select in one launch, for the calls that count
+// nothing and have at most kPPFuseBlocks chunks: the block that finishes its
+// weight sum last draws (a counter behind a fence; every block ends whether
+// it draws or not).  A seed of a small table is three launches of a few
+// microseconds each: 4282 x 4, k = 107 took 1.71 ms with them, 1.52 with two;
+// 269K x 216, k = 64 3.21 and 3.01.  Every block's fence writes back and drops
+// its L2's lines, so with many blocks the separate draw is the better one: 4M x
+// 32 (1954 chunks) took 85 us a seed and 120 in one launch.
+constexpr int kPPFuseBlocks = 256;
+
+__global__ __launch_bounds__(kPPThreads) void k_pp_draw(PPArgs P, int t, int table) {
+    __shared__ uint64_t red[kPPThreads / 64];
+    __shared__ uint64_t scan_lds[16];
+    __shared__ int64_t s_pick, s_blk;
+    __shared__ uint64_t s_rem;
+    __shared__ uint32_t s_last;
+    const int tid = threadIdx.x, G = P.G;
+    const int S = weight_scale(__longlong_as_double((long long)P.Mb[t]), P.L);
+    {
+        const int64_t base = (int64_t)blockIdx.x * kPPChunk;
+        double v[kPPPer];
+#pragma unroll
+        for (int q = 0; q < kPPPer; ++q) {
+            const int64_t i = base + q * kPPThreads + tid;
+            v[q] = i < P.n ? P.D2[i] : 0.0;
+        }
+        uint64_t wsum = 0;
+#pragma unroll
+        for (int q = 0; q < kPPPer; ++q) wsum += weight_of(v[q], S);
+        wsum = wave_sum_u64(wsum);
+        if ((tid & 63) == 0) red[tid >> 6] = wsum;
+        __syncthreads();
+        if (tid == 0) {
+            uint64_t a = 0;
+#pragma unroll
+            for (int j = 0; j < kPPThreads / 64; ++j) a += red[j];
+            __hip_atomic_store(P.bs + blockIdx.x, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __threadfence();
+            s_last = atomicAdd(P.done, 1u);
+        }
+        __syncthreads();
+    }
+    if (s_last != (uint32_t)(G - 1)) return;
+    __threadfence();   // every block's sum is in
+    auto sum_of = [&](int b) { return __hip_atomic_load(P.bs + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    constexpr int kPer = kPPFuseBlocks / kPPThreads;
+    const int per = (G + kPPThreads - 1) / kPPThreads;
+    uint64_t part = 0, bv[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int b = tid * per + q;
+        bv[q] = q < per && b < G ? sum_of(b) : 0;
+        part += bv[q];
+    }
+    uint64_t W = 0;
+    const uint64_t incl = block_scan_u64(part, scan_lds, &W);
+    const double u = P.u[t + 1];
+    if (tid == 0) {
+        *P.done = 0;   // ready for the next draw
+        s_pick = uniform_index(u, P.n);   // W = 0: every point lies on a seed
+        s_blk = -1;
+        s_rem = 0;
+    }
+    __syncthreads();
+    if (W > 0) {
+        uint64_t T = (uint64_t)(u * (double)W);
+        if (T >= W) T = W - 1;
+        uint64_t run = incl - part;
+        if (part > 0 && run <= T && T < incl) {   // exactly one thread
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const uint64_t nx = run + bv[q];
+                if (run <= T && T < nx) {
+                    s_blk = tid * per + q;
+                    s_rem = T - run;
+                }
+                run = nx;
+            }
+        }
+        __syncthreads();
+        const int64_t blk = s_blk;
+        if (blk >= 0) {   // always, as the block sums add up to W
+            const int64_t i0 = blk * kPPChunk + (int64_t)kPPPer * tid;
+            uint64_t wv[kPPPer], ws = 0;
+#pragma unroll
+            for (int q = 0; q < kPPPer; ++q) {
+                wv[q] = i0 + q < P.n ? weight_of(P.D2[i0 + q], S) : 0;
+                ws += wv[q];
+            }
+            uint64_t tot = 0;
+            const uint64_t inc2 = block_scan_u64(ws, scan_lds, &tot);
+            const uint64_t R = s_rem;
+            uint64_t r2 = inc2 - ws;
+            if (ws > 0 && r2 <= R && R < inc2) {
+#pragma unroll
+                for (int q = 0; q < kPPPer; ++q) {
+                    if (r2 <= R && R < r2 + wv[q]) s_pick = i0 + q;
+                    r2 += wv[q];
+                }
+            }
+        }
+    }
+    __syncthreads();
+    put_seed(P, t, s_pick, table);
+}
+
 // Set-up: seed 0 (drawn on the host), the per-step max slots and counters.
 __global__ __launch_bounds__(256) void k_pp_init(PPArgs P, int64_t i0) {
     const int tid = threadIdx.x;
     if (tid == 0) P.idx[0] = i0;
+    if (tid == 0 && P.done) *P.done = 0;
     for (int m = tid; m < P.d; m += blockDim.x) P.C[m] = P.X[i0 * P.d + m];
     for (int j = tid; j < P.k; j += blockDim.x) {
         P.Mb[j] = 0;
@@ -335,23 +464,9 @@ __global__ __launch_bounds__(kPPSelThreads) void k_pp_select(PPArgs P, int t, in
         }
     }
     __syncthreads();
-    const int64_t pick = s_pick;
-    const int d = P.d;
-    if (tid == 0) P.idx[t + 1] = pick;
-    const float* __restrict__ xp = P.X + pick * d;
-    for (int m = tid; m < d; m += kPPSelThreads) P.C[(int64_t)(t + 1) * d + m] = xp[m];
-    // Small seed-to-seed tables are formed here (one thread per earlier
-    // seed; as in k_pp_dcc), larger ones by k_pp_dcc over the chip.
-    if (!table) return;
-    for (int a = tid; a <= t; a += kPPSelThreads) {
-        const float* __restrict__ ca = P.C + (int64_t)a * d;
-        double acc = 0.0;
-        for (int m = 0; m < d; ++m) {
-            const double e = (double)ca[m] - (double)xp[m];
-            acc = fma(e, e, acc);
-        }
-        P.dcc[a] = acc * (1.0 - 0x1p-28);
-    }
+    // Small seed-to-seed tables are formed here, larger ones by k_pp_dcc over
+    // the chip.
+    put_seed(P, t, s_pick, table);
 }
 
 // Seed-to-seed table for the pass with seed t + 1: a lower bound of
@@ -434,13 +549,19 @@ hipError_t launch_pp_seed(const PPArgs& P, int64_t i0, int vw, hipEvent_t* ev, i
     e = P.prune ? step_vec<true, true>(P, 0, vw, s) : step_vec<true, false>(P, 0, vw, s);
     if (e != hipSuccess || (e = mark(0)) != hipSuccess) return e;
     if (P.k == 1) return hipSuccess;
-    hipLaunchKernelGGL(k_pp_weights, dim3((unsigned)P.G), dim3(kPPThreads), 0, s, P, 0);
-    if ((e = hipGetLastError()) != hipSuccess || (e = mark(2)) != hipSuccess) return e;
+    const bool fuse = P.done && P.G <= kPPFuseBlocks;
+    if (!fuse) {
+        hipLaunchKernelGGL(k_pp_weights, dim3((unsigned)P.G), dim3(kPPThreads), 0, s, P, 0);
+        if ((e = hipGetLastError()) != hipSuccess || (e = mark(2)) != hipSuccess) return e;
+    }
     int G = 1;   // lanes per earlier seed in k_pp_dcc
     while (G < 64 && 16 * G < P.d) G *= 2;
     for (int t = 0; t + 1 < P.k; ++t) {
         const bool own = P.prune && (int64_t)(t + 1) * P.d > kPPTableInline;
-        hipLaunchKernelGGL(k_pp_select, dim3(1), dim3(kPPSelThreads), 0, s, P, t, (P.prune && !own) ? 1 : 0);
+        if (fuse)
+            hipLaunchKernelGGL(k_pp_draw, dim3((unsigned)P.G), dim3(kPPThreads), 0, s, P, t, (P.prune && !own) ? 1 : 0);
+        else
+            hipLaunchKernelGGL(k_pp_select, dim3(1), dim3(kPPSelThreads), 0, s, P, t, (P.prune && !own) ? 1 : 0);
         if ((e = hipGetLastError()) != hipSuccess || (e = mark(2)) != hipSuccess) return e;
         if (own) {
             const int64_t thr = (int64_t)(t + 1) * G;
@@ -451,7 +572,7 @@ hipError_t launch_pp_seed(const PPArgs& P, int64_t i0, int vw, hipEvent_t* ev, i
         const int tn = t + 1;   // pass with the new seed, then the weights of the next draw
         e = P.prune ? step_vec<false, true>(P, tn, vw, s) : step_vec<false, false>(P, tn, vw, s);
         if (e != hipSuccess || (e = mark(1)) != hipSuccess) return e;
-        if (tn + 1 < P.k) {
+        if (tn + 1 < P.k && !fuse) {
             hipLaunchKernelGGL(k_pp_weights, dim3((unsigned)P.G), dim3(kPPThreads), 0, s, P, tn);
             if ((e = hipGetLastError()) != hipSuccess || (e = mark(2)) != hipSuccess) return e;
         }
