@@ -584,7 +584,8 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
             (rc2 = c->alloc(&L.fcnt, (size_t)km::kFullCap)) ||
             (rc2 = c->alloc(&L.mv, (size_t)L.mvcap)) || (rc2 = c->alloc(&v.sums, (size_t)k * d + k)) ||
             (rc2 = c->alloc(&L.cs, (size_t)L.nct * km::kLgN * L.nch * 16)) ||
-            (rc2 = c->alloc(&L.cn2p, (size_t)L.nct * km::kLgN)) || (rc2 = c->alloc(&L.smin, (size_t)km::kLgTableSplit * k)) ||
+            (rc2 = c->alloc(&L.cn2p, (size_t)L.nct * km::kLgN)) ||
+            (rc2 = c->alloc(&L.smin, (size_t)((k + km::kLgTableCols - 1) / km::kLgTableCols) * k)) ||
             (rc2 = c->alloc(&L.cand, (size_t)n * L.nct * 16)))
             return rc2;
         zr.add(L.nsurv, 4 * sizeof(uint32_t));
@@ -626,7 +627,7 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
     }
     // The streaming path keeps C^t in two slots (t % 2); slot 0 holds C0.
     if ((rc = c->alloc(&v.C64, (size_t)k * d * (c->small ? 2 : 1))) || (rc = c->alloc(&v.C32, (size_t)k * d)) ||
-        (rc = c->alloc(&v.ec, (size_t)k)) || (rc = c->alloc(&v.h, (size_t)k * k)) ||
+        (rc = c->alloc(&v.ec, (size_t)k)) || (!c->large && (rc = c->alloc(&v.h, (size_t)k * k))) ||
         (rc = c->alloc(&v.s, (size_t)k)) || (rc = c->alloc(&v.f, (size_t)k)) ||
         (rc = c->alloc(&v.cn2, (size_t)k)) ||
         (rc = c->alloc(&v.part, (size_t)v.G * v.L)) || (rc = c->alloc(&v.total, (size_t)v.L)) ||

@@ -63,7 +63,7 @@ struct Dev {
     double* C64;          // k*d master centroids
     float* C32;           // k*d float32 copy used for distances
     float* ec;            // k: ||c32_j - c64_j|| rounded up
-    float* h;             // k*k: half centroid distances rounded down
+    float* h;             // k*k: half centroid distances rounded down (null on the global path)
     float* s;             // k: min_{j != i} h[i][j] rounded down (+inf if k == 1)
     float* f;             // k: drift ||c_j^t - c_j^{t-1}|| rounded up
     float* cn2;           // k: ||c32_j||^2 (matrix-core path)
@@ -105,7 +105,7 @@ constexpr int kLgBoundThreads = 1024;                 // threads per block of th
 constexpr int kLgBoundWaves = kLgBoundThreads / 64;
 constexpr int kLgBoundRounds = 4;                     // rounds of kLgBoundThreads points per block
 constexpr int kLgBoundSpan = kLgBoundThreads * kLgBoundRounds;
-constexpr int kLgTableSplit = 4;     // block columns (centroid ranges) of the tiled centroid table
+constexpr int kLgTableCols = 64;     // centroids per block column of the tiled centroid table
 constexpr int kLgMaxD = 4096;        // largest d of the global-memory path
 
 // Split rows (the matrix-core operands of the global path): every float32
@@ -147,7 +147,7 @@ struct Large {
     int32_t mvcap;        // at most this many moves: incremental sums, else full sums
     uint32_t* cs;         // nct * kLgN split rows of the float32 centroids (rows >= k zero)
     float* cn2p;          // nct * kLgN: their float32 squared norms (rows >= k: +inf)
-    float* smin;          // kLgTableSplit x k: column minima of the half-distance table (reduced to s)
+    float* smin;          // (k / kLgTableCols) x k: column minima of the half-distance table (reduced to s)
     uint32_t* cand;       // n x nct x 4 x 4: per survivor, centroid tile and quarter of it (half tile, half-wave), the
                           // four smallest expanded distances as ascending keys (float bits, the low 8 the place)
     int32_t nch;          // chunks per split row

@@ -40,8 +40,9 @@ namespace km {
 
 namespace {
 
-constexpr int kTiTile = 16;   // centroid rows per block of the tiled centroid table
-constexpr int kTiSplit = kLgTableSplit;
+constexpr int kTiTile = 16;          // centroid rows per block of the tiled centroid table
+constexpr int kTiCols = kLgTableCols; // centroids per block column
+constexpr int kTiK = 16;             // dimensions staged at a time
 constexpr int kRefineFlush = 128;   // LDS entries of the refinement pass that trigger a flush
 
 // Adds each of n counters (summed over the block) to its slot of the step's
@@ -187,11 +188,14 @@ __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ sr
         for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
         if (lane == 0) {
             norms[r] = pad ? INFINITY : sq;
-            if (smin && !pad) {   // min over j != r of the half distances: the table's column minima
-                float m = INFINITY;
-                for (int y = 0; y < kTiSplit; ++y) m = fminf(m, smin[(int64_t)y * valid + r]);
-                s_out[r] = m;
-            }
+        }
+        if (smin && !pad) {   // min over j != r of the half distances: the table's column minima
+            float m = INFINITY;
+            for (int y = lane; y < (int)((valid + kTiCols - 1) / kTiCols); y += 64)
+                m = fminf(m, smin[(int64_t)y * valid + r]);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) m = fminf(m, __shfl_xor(m, off));
+            if (lane == 0) s_out[r] = m;
         }
     }
 }
@@ -1147,83 +1151,85 @@ __global__ __launch_bounds__(256) void k_moves_large(Dev P_, Large Lg) {
 }
 
 // ---------------------------------------------------------------------------
-// Centroid table for large k*d: a block stages kTiTile float64 rows in LDS
-// and streams every centroid once against them.
+// Centroid table for large k*d: the minima s of the half distances (the
+// distances themselves are not kept; this path tests Clause 1 only).  A block
+// takes kTiTile rows against kTiCols centroids, kTiK dimensions at a time
+// staged in LDS from coalesced loads (the next ones in registers); a lane
+// forms four rows' distances to one centroid.  Bound by float64 vector work,
+// 2 k^2 d of it, at k = 1000 and by latency at a few hundred centroids.  With
+// four block columns whatever k, a lane per centroid reading its own row, and
+// each row's norm summed by one lane, 16 rows against 250 centroids took 77 us
+// at k = 1000, d = 256 and 37 us at k = 200, d = 128; now 49 and 13 us.
 
 __global__ __launch_bounds__(256) void k_centroid_table_tiled(Dev P, Large Lg, int force) {
     if (!force && !P.st->active) return;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {   // the next step's lists start empty
+    const int tid = threadIdx.x, lane = tid & 63, rg = tid >> 6;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {   // the next step's lists start empty
         *Lg.nsurv = 0;
         *Lg.nfull = 0;
         *Lg.nmq = 0;
         *Lg.nmv = 0;
     }
-    if (P.iterm && !force && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 64) close_inertia(P);
+    if (P.iterm && !force && blockIdx.x == 0 && blockIdx.y == 0 && tid < 64) close_inertia(P);
     const int k = P.k, d = P.d;
-    const int i0 = blockIdx.x * kTiTile, ni = min(kTiTile, k - i0);
-    // Block column y takes centroids j in [y k / kTiSplit, (y + 1) k / kTiSplit).
-    const int j0 = (int)((int64_t)blockIdx.y * k / kTiSplit), j1 = (int)((int64_t)(blockIdx.y + 1) * k / kTiSplit);
-    extern __shared__ __align__(16) unsigned char smem[];
-    double* ci = reinterpret_cast<double*>(smem);                  // [kTiTile][d]
-    float* mins = reinterpret_cast<float*>(ci + kTiTile * d);      // [kTiTile][256]
-    for (int e = threadIdx.x; e < kTiTile * d; e += blockDim.x) {
-        const int r = e / d;
-        ci[e] = r < ni ? P.C64[(int64_t)(i0 + r) * d + (e - r * d)] : 0.0;
-    }
-    __syncthreads();
-    float mn[kTiTile];
+    const int i0 = blockIdx.x * kTiTile, j0 = blockIdx.y * kTiCols;
+    __shared__ double A[kTiTile][kTiK + 1], B[kTiCols][kTiK + 1];
+    const int sr = tid >> 4, sm = tid & 15;   // this lane's row (of 16) and dimension in a staged piece
+    auto at = [&](int r, int m) __attribute__((always_inline)) {
+        return r < k && m < d ? P.C64[(int64_t)r * d + m] : 0.0;
+    };
+    double na, nb[kTiCols / 16];
+    auto load = [&](int m0) __attribute__((always_inline)) {
+        na = at(i0 + sr, m0 + sm);
 #pragma unroll
-    for (int r = 0; r < kTiTile; ++r) mn[r] = INFINITY;
-    for (int j = j0 + threadIdx.x; j < j1; j += blockDim.x) {
-        const double* cj = P.C64 + (int64_t)j * d;
-        double acc[kTiTile];
+        for (int q = 0; q < kTiCols / 16; ++q) nb[q] = at(j0 + 16 * q + sr, m0 + sm);
+    };
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    load(0);
+    for (int m0 = 0; m0 < d; m0 += kTiK) {
+        __syncthreads();
+        A[sr][sm] = na;
 #pragma unroll
-        for (int r = 0; r < kTiTile; ++r) acc[r] = 0.0;
-        for (int m = 0; m < d; ++m) {
-            const double v = cj[m];
+        for (int q = 0; q < kTiCols / 16; ++q) B[16 * q + sr][sm] = nb[q];
+        __syncthreads();
+        if (m0 + kTiK < d) load(m0 + kTiK);
 #pragma unroll
-            for (int r = 0; r < kTiTile; ++r) {
-                const double t = ci[r * d + m] - v;
+        for (int m = 0; m < kTiK; ++m) {   // zero past d
+            const double b = B[lane][m];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double t = A[4 * rg + r][m] - b;
                 acc[r] = fma(t, t, acc[r]);
             }
         }
-#pragma unroll
-        for (int r = 0; r < kTiTile; ++r) {
-            if (r >= ni) continue;
-            const int i = i0 + r;
-            float hv = 0.f;
-            if (j != i) {
-                hv = f32_down(0.5 * sqrt(acc[r]) * (1.0 - 0x1p-40));
-                mn[r] = fminf(mn[r], hv);
-            }
-            P.h[(int64_t)i * k + j] = hv;
-        }
     }
+    const int j = j0 + lane;
 #pragma unroll
-    for (int r = 0; r < kTiTile; ++r) mins[r * 256 + threadIdx.x] = mn[r];
-    __syncthreads();
-    if (threadIdx.x < ni) {   // this column's minimum; k_split_rows forms s from the columns
-        const int r = threadIdx.x, i = i0 + r;
-        float m = INFINITY;
-        for (int q = 0; q < (int)blockDim.x; ++q) m = fminf(m, mins[r * 256 + q]);
-        Lg.smin[(int64_t)blockIdx.y * k + i] = m;
-        if (blockIdx.y == 0) {
-            const float* c32 = P.C32 + (int64_t)i * d;
-            double n2 = 0.0;
-            for (int q = 0; q < d; ++q) n2 = fma((double)c32[q], (double)c32[q], n2);
-            P.cn2[i] = (float)n2;
-        }
+    for (int r = 0; r < 4; ++r) {   // this column block's minimum; k_split_rows forms s from them
+        const int i = i0 + 4 * rg + r;
+        float hv = j < k && j != i ? f32_down(0.5 * sqrt(acc[r]) * (1.0 - 0x1p-40)) : INFINITY;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) hv = fminf(hv, __shfl_xor(hv, off));
+        if (lane == 0 && i < k) Lg.smin[(int64_t)blockIdx.y * k + i] = hv;
+    }
+    if (blockIdx.y == 0) {   // the rows' float32 squared norms, 16 lanes each
+        const int i = min(i0 + sr, k - 1);
+        const float* c32 = P.C32 + (int64_t)i * d;
+        double n2 = 0.0;
+        for (int m = sm; m < d; m += 16) n2 = fma((double)c32[m], (double)c32[m], n2);
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) n2 += __shfl_xor(n2, off);
+        if (sm == 0 && i0 + sr < k) P.cn2[i] = (float)n2;
     }
     if (blockIdx.x == 0 && blockIdx.y == 0) {
+        __shared__ float mx[4];
         float em = 0.f;
-        for (int j = threadIdx.x; j < k; j += blockDim.x) em = fmaxf(em, P.ec[j]);
+        for (int q = tid; q < k; q += 256) em = fmaxf(em, P.ec[q]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) em = fmaxf(em, __shfl_xor(em, off));
+        if (lane == 0) mx[rg] = em;
         __syncthreads();
-        if ((threadIdx.x & 63) == 0) mins[threadIdx.x >> 6] = em;
-        __syncthreads();
-        if (threadIdx.x == 0)
-            P.st->ec_max = fmaxf(fmaxf(mins[0], mins[1]), fmaxf(mins[2], mins[3]));
+        if (tid == 0) P.st->ec_max = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
     }
 }
 
@@ -1265,7 +1271,9 @@ hipError_t launch_large_reduce(const Dev& dv, const Large& lg, hipStream_t s) {
     return hipGetLastError();
 }
 
-int large_table_lds(int d) { return 8 * kTiTile * d + 4 * kTiTile * 256; }
+// The widths the path has taken so far: those whose rows, 16 at a time, fit in
+// LDS as float64 (the table no longer needs it).
+int large_table_lds(int d) { return 128 * d + 16384; }
 
 hipError_t large_set_attributes(int k, int d) {
     hipError_t e;
@@ -1275,15 +1283,12 @@ hipError_t large_set_attributes(int k, int d) {
         return e;
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hist_large), attr, 4 * k)) != hipSuccess)
         return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_scatter_large), attr, 4 * k)) != hipSuccess)
-        return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_centroid_table_tiled), attr,
-                               large_table_lds(d));
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_scatter_large), attr, 4 * k);
 }
 
 hipError_t launch_large_table(const Dev& dv, const Large& lg, int force, hipStream_t s) {
-    hipLaunchKernelGGL(k_centroid_table_tiled, dim3((dv.k + kTiTile - 1) / kTiTile, kTiSplit), dim3(256),
-                       large_table_lds(dv.d), s, dv, lg, force);
+    hipLaunchKernelGGL(k_centroid_table_tiled, dim3((dv.k + kTiTile - 1) / kTiTile, (dv.k + kTiCols - 1) / kTiCols),
+                       dim3(256), 0, s, dv, lg, force);
     const int64_t kp = (int64_t)lg.nct * kLgN;   // padded to whole centroid tiles
     hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((kp + 3) / 4)), dim3(256), 0, s, static_cast<const float*>(dv.C32),
                        kp, (int64_t)dv.k, dv.d, lg.nch, lg.cs, lg.cn2p, static_cast<const IterState*>(dv.st), force,
