@@ -141,8 +141,8 @@ void pinned_give(int32_t* p) {
     (void)hipHostFree(p);
 }
 
-// Launch configuration of a kernel: its dynamic-LDS limit raised to lds
-// bytes and the resident blocks per CU for (block, lds), both remembered per
+// Launch configuration of a kernel: its dynamic-LDS limit raised and the
+// resident blocks per CU for (block, lds), both remembered per
 // device (hipFuncSetAttribute costs tens of microseconds a call).
 struct KernelCfg {
     int dev;
@@ -163,7 +163,11 @@ int kernel_config(int dev, const void* sym, int block, int lds, int* per_cu) {
                 return KM_OK;
             }
     }
-    KM_HIP(hipFuncSetAttribute(sym, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    // The limit is one per kernel: raised to the device's, not to this shape's
+    // need, since shapes of different need alternate on one kernel.
+    int lim = 0;
+    KM_HIP(hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    KM_HIP(hipFuncSetAttribute(sym, hipFuncAttributeMaxDynamicSharedMemorySize, lim));
     int pc = 0;
     KM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, sym, block, lds));
     std::lock_guard<std::mutex> lock(g_cfg_mu);

@@ -135,3 +135,15 @@ def test_inertia_from_exact_sums(n, d, k, kw):
         assert ctx.history()["inertia"][-1] == ctx.stats()["inertia_last"]
         if k == n:
             assert ctx.stats()["inertia_last"] == 0.0
+
+
+def test_shapes_of_different_lds_need_alternate_on_one_kernel():
+    # one kernel (two centroid blocks, aligned rows, d > 32) at 108, 54 and 108 KB
+    # of LDS: its limit must not follow the last shape that set it
+    runs = {}
+    for d, k in ((100, 60), (36, 33), (100, 60), (36, 33)):
+        X, C0 = synth.blobs(2000, d, k, seed=851 + d, spread=4.0, sigma=1.5)
+        a, c, _ = _same(_gpu(X), _gpu(C0), 6)
+        if (d, k) in runs:
+            assert torch.equal(runs[(d, k)][0], a) and torch.equal(runs[(d, k)][1], c)
+        runs[(d, k)] = (a, c)
