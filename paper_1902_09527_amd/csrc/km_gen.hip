@@ -693,33 +693,79 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
             const float band = 2.f * gamma * (d1 + d2) + 4.f * (sqrtf(d1) + sqrtf(d2)) * ecmax + 8.f * ecmax * ecmax;
             re = d2 - d1 <= band;
         }
-        for (uint64_t rm = __ballot(re); rm; rm &= rm - 1) {
-            const int l = __builtin_ctzll(rm);
-            const int pa = __shfl(p, l), ia = __shfl(inc, l), oa = __shfl(o0, l), ta = __shfl(tot, l);
-            const float* xr = P.X + (int64_t)pa * d;
-            double Dbb = INFINITY;
-            int kb = INT_MAX, bb = -1;
-            for (int i = 0; i < (ta ? ta : k); ++i) {
-                const int j = ta ? (int)(wl->pl[oa + i] & 255u) : i;
-                const double* cr = P.C64 + (int64_t)j * d;
-                double Dj = 0.0;
-                for (int m = lane; m < d; m += 64) {
-                    const double t = (double)xr[m] - cr[m];
-                    Dj = fma(t, t, Dj);
+        // Float64 against the master centroids, every distance summed over the
+        // dimensions in order by one lane as on the other paths: rows at equal
+        // distances from two centroids then fall alike on all of them.
+        if (d <= kGenLaneD) {   // a lane per row
+            if (re) {
+                const float* xr = P.X + (int64_t)p * d;
+                double Dbb = INFINITY;
+                int kb = INT_MAX, bb = -1;
+                for (int i = 0; i < (tot ? tot : k); ++i) {
+                    const int j = tot ? (int)(wl->pl[o0 + i] & 255u) : i;
+                    const double Dj = sqd64(xr, P.C64 + (int64_t)j * d, d);
+                    const int rk = j == inc ? -1 : j;
+                    if (Dj < Dbb || (Dj == Dbb && rk < kb)) {
+                        Dbb = Dj;
+                        kb = rk;
+                        bb = j;
+                    }
                 }
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) Dj += __shfl_xor(Dj, o);
-                const int rk = j == ia ? -1 : j;
-                if (Dj < Dbb || (Dj == Dbb && rk < kb)) {
-                    Dbb = Dj;
-                    kb = rk;
-                    bb = j;
-                }
-            }
-            if (lane == l) {
                 b = bb < 0 ? 0 : bb;
                 ub = f32_up(sqrt(Dbb) * (1.0 + 0x1p-40));
                 my_rc += 1;
+            }
+        } else {
+            for (uint64_t rm = __ballot(re); rm; rm &= rm - 1) {
+                const int l = __builtin_ctzll(rm);
+                const int pa = __shfl(p, l), ia = __shfl(inc, l), oa = __shfl(o0, l), ta = __shfl(tot, l);
+                const float* xr = P.X + (int64_t)pa * d;
+                double Dbb = INFINITY;
+                int kb = INT_MAX, bb = -1;
+                auto take64 = [&](double D, int rk, int j) __attribute__((always_inline)) {
+                    if (D < Dbb || (D == Dbb && rk < kb)) {
+                        Dbb = D;
+                        kb = rk;
+                        bb = j;
+                    }
+                };
+                // Few candidates: the whole wave forms one distance after
+                // another, which decides unless the two smallest lie within
+                // the rounding of the sums.
+                bool order = ta == 0;
+                if (ta) {
+                    double D2 = INFINITY;
+                    for (int i = 0; i < ta; ++i) {
+                        const int j = (int)(wl->pl[oa + i] & 255u);
+                        const double* cr = P.C64 + (int64_t)j * d;
+                        double Dj = 0.0;
+                        for (int m = lane; m < d; m += 64) {
+                            const double t = (double)xr[m] - cr[m];
+                            Dj = fma(t, t, Dj);
+                        }
+#pragma unroll
+                        for (int o = 32; o > 0; o >>= 1) Dj += __shfl_xor(Dj, o);
+                        D2 = fmin(D2, fmax(Dj, Dbb));
+                        take64(Dj, j == ia ? -1 : j, j);
+                    }
+                    order = !(D2 - Dbb > 0x1p-40 * D2);   // (two orders differ by 2 (d + 6) 2^-53 of it, d <= 1024)
+                }
+                if (order) {   // a lane per centroid
+                    Dbb = INFINITY;
+                    kb = INT_MAX;
+                    bb = -1;
+                    for (int i = lane; i < (ta ? ta : k); i += 64) {
+                        const int j = ta ? (int)(wl->pl[oa + i] & 255u) : i;
+                        take64(sqd64(xr, P.C64 + (int64_t)j * d, d), j == ia ? -1 : j, j);
+                    }
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) take64(__shfl_xor(Dbb, o), __shfl_xor(kb, o), __shfl_xor(bb, o));
+                }
+                if (lane == l) {
+                    b = bb < 0 ? 0 : bb;
+                    ub = f32_up(sqrt(Dbb) * (1.0 + 0x1p-40));
+                    my_rc += 1;
+                }
             }
         }
         const bool moved = live && b != inc;

@@ -499,6 +499,7 @@ __host__ __device__ inline GenVecLds gen_vec_lds(int DP, int d, int k) {
 // candidates are listed with up to kGenCand of them (more: all centroids) and
 // decided once kGenList of them or kGenPairs (survivor, candidate) pairs wait.
 constexpr int kGenCand = 6, kGenList = 32, kGenPairs = 128;
+constexpr int kGenLaneD = 16;         // up to this d a listed survivor's float64 decision is one lane's work
 struct GenMatWave {
     uint2 q[96];          // survivors (point, state): one batch of 32 short of full and a sub-step of 64 points
     uint2 ml[64];         // moves being applied

@@ -847,17 +847,35 @@ __global__ __launch_bounds__(256) void k_multi_large(Dev P, Large Lg) {
         int b = j1;
         float ub = upper_bound(d1, P.ec[j1], gamma);
         if (re) {
-            double Dbb = INFINITY;
+            double Dbb = INFINITY, D2 = INFINITY;
             int bb = -1, kb = INT_MAX;
-            for (int t = 0; t < nq; ++t) {
-                const int j = js(t);
-                const double Dj = dist64(j);
-                const int rk = j == inc ? -1 : j;
-                if (Dj < Dbb || (Dj == Dbb && rk < kb)) {
-                    Dbb = Dj;
+            auto take64 = [&](double D, int rk, int j) __attribute__((always_inline)) {
+                if (D < Dbb || (D == Dbb && rk < kb)) {
+                    Dbb = D;
                     bb = j;
                     kb = rk;
                 }
+            };
+            for (int t = 0; t < nq; ++t) {
+                const int j = js(t);
+                const double Dj = dist64(j);
+                D2 = fmin(D2, fmax(Dj, Dbb));
+                take64(Dj, j == inc ? -1 : j, j);
+            }
+            if (!(D2 - Dbb > 0x1p-40 * D2)) {
+                // within the rounding of the sums (two orders differ by 2 (d +
+                // 6) 2^-53): summed over the dimensions in order, a lane per
+                // candidate, as on the other paths, so that rows at equal
+                // distances from two centroids fall alike on all of them
+                Dbb = INFINITY;
+                bb = -1;
+                kb = INT_MAX;
+                if (lane < nq) {
+                    const int j = js(lane);
+                    take64(sqd64(xr, P.C64 + (int64_t)j * d, d), j == inc ? -1 : j, j);
+                }
+#pragma unroll
+                for (int o = 4; o > 0; o >>= 1) take64(__shfl_xor(Dbb, o), __shfl_xor(kb, o), __shfl_xor(bb, o));
             }
             b = bb < 0 ? 0 : bb;
             ub = f32_up(sqrt(Dbb) * (1.0 + 0x1p-40));

@@ -147,3 +147,19 @@ def test_shapes_of_different_lds_need_alternate_on_one_kernel():
         if (d, k) in runs:
             assert torch.equal(runs[(d, k)][0], a) and torch.equal(runs[(d, k)][1], c)
         runs[(d, k)] = (a, c)
+
+
+@pytest.mark.parametrize("n,d,k,large", [(16000, 6, 138, False), (12000, 5, 60, False), (12000, 24, 60, False),
+                                         (6000, 40, 90, False), (21000, 17, 294, False), (9000, 6, 50, True)],
+                         ids=lambda v: str(v))
+def test_tied_rows_fall_alike_on_every_path(n, d, k, large):
+    # whole numbers projected to the unit sphere: many rows at equal distances
+    # from two centroids, their float64 sums equal only when formed in one order
+    rng = np.random.default_rng(861 + d)
+    X = np.round(rng.normal(0.0, 1.2, (n, d))).astype(np.float32)
+    X[np.abs(X).sum(1) == 0, 0] = 1.0
+    Xg, Cg = _gpu(X), _gpu(X[rng.permutation(n)[:k]])
+    a1, c1, s1 = km.run(Xg, Cg, 10, spherical=True, large_path=large)
+    a2, c2, s2 = km.run(Xg, Cg, 10, spherical=True, generic=True)
+    assert torch.equal(a1, a2) and torch.equal(c1.view(torch.int32), c2.view(torch.int32))
+    assert s1["changed_last"] == s2["changed_last"]
