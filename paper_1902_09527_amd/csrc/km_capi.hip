@@ -336,7 +336,7 @@ int enqueue_iteration(km_ctx* c) {
         c->stepped = true;
         return KM_OK;
     }
-    e = c->gen     ? km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, c->enq == 0 ? 1 : 0, c->stream)
+    e = c->gen     ? km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, c->stream)
         : c->large ? km::launch_large_assign(c->dv, c->lg, c->gb, c->stream)
                    : km::launch_assign(c->dv, c->variant, c->tp, c->lds, c->stream);
     if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "assign kernel"));

@@ -141,9 +141,10 @@ __device__ __forceinline__ void flush_block(const Dev& P, const uint64_t* acc, c
 // (the survivors' lines and the states are 0.5 ms at 4.8 TB/s).
 
 template <int DP>
-__global__ __launch_bounds__(kGenThreads) void k_inc_vec(Dev P_, int first, int nsub) {
+__global__ __launch_bounds__(kGenThreads) void k_inc_vec(Dev P_, int nsub) {
     const Dev P = with_scales(P_);
     IterState* st = P.st;
+    const bool first = st->t == 0;   // from the device: a captured step can be replayed as any step
     if (st->done) {
         if (blockIdx.x == 0 && threadIdx.x == 0) st->active = 0;
         return;
@@ -441,9 +442,10 @@ template <int KB, bool ONE>
 constexpr int gen_mat_steps() { return ONE || KB >= 4 ? 2 : 4; }
 
 template <int KB, bool VEC, bool ONE>
-__global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_waves_per_eu(gen_mat_waves(KB, ONE) / 4))) void k_inc_mat(Dev P_, int first, int nsub) {
+__global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_waves_per_eu(gen_mat_waves(KB, ONE) / 4))) void k_inc_mat(Dev P_, int nsub) {
     const Dev P = with_scales(P_);
     IterState* st = P.st;
+    const bool first = st->t == 0;
     if (st->done) {
         if (blockIdx.x == 0 && threadIdx.x == 0) st->active = 0;
         return;
@@ -1294,9 +1296,9 @@ const void* gen_symbol(GenKind kind, const Dev& dv) {
 #undef KM_M
 }
 
-hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, int first, hipStream_t s) {
-#define KM_V(DP_) { hipLaunchKernelGGL(k_inc_vec<DP_>, dim3(grid), dim3(kGenThreads), lds_bytes, s, dv, first, nsub); }
-#define KM_M(KB_, V_, O_) { hipLaunchKernelGGL((k_inc_mat<KB_, V_, O_>), dim3(grid), dim3(64 * gen_mat_waves(KB_, O_)), lds_bytes, s, dv, first, nsub); }
+hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, hipStream_t s) {
+#define KM_V(DP_) { hipLaunchKernelGGL(k_inc_vec<DP_>, dim3(grid), dim3(kGenThreads), lds_bytes, s, dv, nsub); }
+#define KM_M(KB_, V_, O_) { hipLaunchKernelGGL((k_inc_mat<KB_, V_, O_>), dim3(grid), dim3(64 * gen_mat_waves(KB_, O_)), lds_bytes, s, dv, nsub); }
     KM_GEN_CASES(KM_V, KM_M)
 #undef KM_V
 #undef KM_M

@@ -163,3 +163,26 @@ def test_tied_rows_fall_alike_on_every_path(n, d, k, large):
     a2, c2, s2 = km.run(Xg, Cg, 10, spherical=True, generic=True)
     assert torch.equal(a1, a2) and torch.equal(c1.view(torch.int32), c2.view(torch.int32))
     assert s1["changed_last"] == s2["changed_last"]
+
+
+@pytest.mark.parametrize("n,d,k,kw", [(3001, 7, 9, {}), (5000, 24, 40, {}), (4000, 5, 129, {"stats": True}),
+                                      (3000, 5, 257, {}), (3000, 24, 40, {"generic": True})], ids=lambda v: str(v))
+def test_captured_step_replays_as_every_step(n, d, k, kw):
+    # the first call to iterate recorded into a graph: its replays are the
+    # first, second, ... step, with eager work and synchronizations between
+    X, C0 = synth.blobs(n, d, k, seed=871 + d, spread=4.0, sigma=1.5, comps=max(1, k // 2))
+    Xg, Cg = _gpu(X), _gpu(C0)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s), km.KMeansMTI(Xg, Cg, **kw) as ctx, km.KMeansMTI(Xg, Cg, **kw) as ref:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            ctx.iterate()
+        for t in range(6):
+            graph.replay()
+            s.synchronize()
+            ref.iterate(sync=True)
+            a, c = ctx.get()
+            b, e = ref.get()
+            s.synchronize()
+            assert torch.equal(a, b) and torch.equal(c.view(torch.int32), e.view(torch.int32)), t
+        assert ctx.stats()["iterations"] == 6 and ctx.stats()["dist_computed"] == ref.stats()["dist_computed"]
