@@ -576,7 +576,12 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
     // Queued survivors and moves gather in LDS and go to the global lists
     // with one atomic per flush of up to 2 kRefineFlush entries (a global
     // counter per wave would take one atomic per 64 survivors).
-    __shared__ int4 qb[2 * kRefineFlush], mb[2 * kRefineFlush];
+    // A queued survivor: its list entry, and the ids of its candidates (0xffff
+    // past them).  The lanes of its group write disjoint words, so nothing
+    // orders their stores before the barrier of the flush.
+    __shared__ int qc[2 * kRefineFlush];
+    __shared__ uint16_t qid[2 * kRefineFlush][kMultiCand];
+    __shared__ int4 mb[2 * kRefineFlush];
     __shared__ uint32_t nqb, nmb, gq, gm;
     if (tid == 0) {
         nqb = 0;
@@ -593,7 +598,10 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
         }
         __syncthreads();
         if (fq)
-            for (uint32_t e = tid; e < cq; e += blockDim.x) Lg.mq[gq + e] = qb[e];
+            for (uint32_t e = tid; e < cq; e += blockDim.x) {
+                auto two = [&](int t) { return (int)((uint32_t)qid[e][t] | (uint32_t)qid[e][t + 1] << 16); };
+                Lg.mq[gq + e] = make_int4(qc[e], two(0), two(2), two(4));
+            }
         if (fm)
             for (uint32_t e = tid; e < cm; e += blockDim.x)
                 if (gm + e < (uint32_t)Lg.mvcap) Lg.mv[gm + e] = mb[e];
@@ -721,14 +729,15 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
             }
             P.u[i] = ub;
         }
-        if (queued) {   // the group appends its ids after the leader's entry
+        if (queued) {   // the group's lanes append the ids they hold, the leader the rest of the entry
             uint32_t e = 0;
             if (lead) {
                 e = atomicAdd(&nqb, 1u);
-                qb[e] = make_int4((int)c, -1, -1, -1);
+                qc[e] = (int)c;
+                for (int t = nq; t < kMultiCand; ++t) qid[e][t] = 0xffffu;
             }
             e = __shfl(e, lane & ~(lps - 1));
-            uint16_t* ids = reinterpret_cast<uint16_t*>(qb + e) + 2;
+            uint16_t* ids = qid[e];
             int done = 0;
             auto put = [&](uint32_t key, int list) __attribute__((always_inline)) {
                 const uint64_t hm = __ballot(within(key));

@@ -186,3 +186,20 @@ def test_captured_step_replays_as_every_step(n, d, k, kw):
             s.synchronize()
             assert torch.equal(a, b) and torch.equal(c.view(torch.int32), e.view(torch.int32)), t
         assert ctx.stats()["iterations"] == 6 and ctx.stats()["dist_computed"] == ref.stats()["dist_computed"]
+
+
+@pytest.mark.parametrize("m", [2, 3, 5, 6, 7])
+def test_global_path_keeps_every_candidate_of_a_survivor(m):
+    # every centroid m times over: each survivor has m candidates (up to six go
+    # on with it, seven are decided over all centroids); the lowest of equal
+    # ones wins the first step
+    n, d, k = 4000, 12, 300
+    X, C0 = synth.blobs(n, d, k, seed=881 + m, spread=4.0, sigma=1.5)
+    C0 = np.repeat(C0[:(k + m - 1) // m], m, axis=0)[:k]
+    Xg, Cg = _gpu(X), _gpu(C0)
+    a1, c1, s1 = km.run(Xg, Cg, 4, large_path=True)
+    a2, c2, s2 = km.run(Xg, Cg, 4, generic=True)
+    assert torch.equal(a1, a2) and torch.equal(c1.view(torch.int32), c2.view(torch.int32))
+    assert s1["rechecks"] >= n
+    a, _, _ = km.run(Xg, Cg, 1, large_path=True)
+    assert int((a % m).max()) == 0
