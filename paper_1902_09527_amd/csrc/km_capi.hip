@@ -141,9 +141,34 @@ void pinned_give(int32_t* p) {
     (void)hipHostFree(p);
 }
 
+// Raises a kernel's dynamic-LDS limit to what its static LDS leaves of the
+// device's, once per device and kernel (the calls cost tens of microseconds).
+// The limit is one per kernel, whatever context launches it: set to one
+// shape's need it would stop a context of a larger shape that is still open.
+struct RaisedLds {
+    int dev;
+    const void* sym;
+};
+constexpr int kRaisedSlots = 256;
+std::mutex g_raised_mu;
+RaisedLds g_raised[kRaisedSlots];
+int g_raised_n = 0;
+
+int raise_lds_limit(int dev, const void* sym) {
+    std::lock_guard<std::mutex> lock(g_raised_mu);
+    for (int i = 0; i < g_raised_n; ++i)
+        if (g_raised[i].dev == dev && g_raised[i].sym == sym) return KM_OK;
+    int lim = 0;
+    hipFuncAttributes fa;
+    KM_HIP(hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    KM_HIP(hipFuncGetAttributes(&fa, sym));
+    KM_HIP(hipFuncSetAttribute(sym, hipFuncAttributeMaxDynamicSharedMemorySize, lim - (int)fa.sharedSizeBytes));
+    if (g_raised_n < kRaisedSlots) g_raised[g_raised_n++] = RaisedLds{dev, sym};
+    return KM_OK;
+}
+
 // Launch configuration of a kernel: its dynamic-LDS limit raised and the
-// resident blocks per CU for (block, lds), both remembered per
-// device (hipFuncSetAttribute costs tens of microseconds a call).
+// resident blocks per CU for (block, lds), remembered per device.
 struct KernelCfg {
     int dev;
     const void* sym;
@@ -163,11 +188,7 @@ int kernel_config(int dev, const void* sym, int block, int lds, int* per_cu) {
                 return KM_OK;
             }
     }
-    // The limit is one per kernel: raised to the device's, not to this shape's
-    // need, since shapes of different need alternate on one kernel.
-    int lim = 0;
-    KM_HIP(hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-    KM_HIP(hipFuncSetAttribute(sym, hipFuncAttributeMaxDynamicSharedMemorySize, lim));
+    if (const int rc = raise_lds_limit(dev, sym)) return rc;
     int pc = 0;
     KM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, sym, block, lds));
     std::lock_guard<std::mutex> lock(g_cfg_mu);
@@ -552,16 +573,16 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
         c->large = true;
         km::Large& L = c->lg;
         const int mlds = km::large_mfma_lds();
-        if (d > km::kLgMaxD || mlds > max_lds || 4 * k > max_lds || km::large_table_lds(d) > max_lds) {
+        if (d > km::kLgMaxD || mlds > max_lds || 4 * k > max_lds) {
             snprintf(g_last_hip, sizeof g_last_hip,
                      "k = %d, d = %d: no kernel path (d <= %d and k <= %d needed)", k, d, km::kLgMaxD,
                      max_lds / 4);
             return KM_ERR_UNSUPPORTED;
         }
-        const void* sym = km::large_mfma_symbol();
-        KM_HIP(km::large_set_attributes(k, d));
-        int per_cu = 0;
-        KM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sym, 256, mlds));
+        int per_cu = 0, rcc;
+        for (int i = 0; i < km::kLgDynamic; ++i)
+            if ((rcc = raise_lds_limit(c->device, km::large_dynamic_symbol(i))) != KM_OK) return rcc;
+        if ((rcc = kernel_config(c->device, km::large_mfma_symbol(), 256, mlds, &per_cu)) != KM_OK) return rcc;
         if (per_cu < 1) return KM_ERR_UNSUPPORTED;
         L.Gm = per_cu * cus;
         L.Gr = 4 * cus;

@@ -106,7 +106,8 @@ constexpr int kLgBoundWaves = kLgBoundThreads / 64;
 constexpr int kLgBoundRounds = 4;                     // rounds of kLgBoundThreads points per block
 constexpr int kLgBoundSpan = kLgBoundThreads * kLgBoundRounds;
 constexpr int kLgTableCols = 64;     // centroids per block column of the tiled centroid table
-constexpr int kLgMaxD = 4096;        // largest d of the global-memory path
+constexpr int kLgMaxD = 1152;        // largest d of the global-memory path
+constexpr int kLgDynamic = 3;        // its kernels beside the matrix-core kernel whose LDS grows with k or d
 
 // Split rows (the matrix-core operands of the global path): every float32
 // value x is held as hi = bf16(x) and lo = bf16(x - hi), both rounded to
@@ -385,10 +386,8 @@ hipError_t launch_large_reduce(const Dev& dv, const Large& lg, hipStream_t s);
 hipError_t launch_large_table(const Dev& dv, const Large& lg, int force, hipStream_t s);
 // Split rows (and, with norms, float32 squared norms) of X, once at set-up.
 hipError_t launch_large_split_x(const Dev& dv, const Large& lg, int cus, hipStream_t s);
-int large_table_lds(int d);
 const void* large_mfma_symbol();   // the matrix-core kernel
-// Raises the dynamic-LDS limits of the global-memory path's kernels.
-hipError_t large_set_attributes(int k, int d);
+const void* large_dynamic_symbol(int i);   // i < kLgDynamic: the others with dynamic LDS
 
 // Kernel launchers (km_kernels.hip).  Each returns the launch status.
 // Set-up magnitude words (out[kAmax*], zero before): the largest |value| of a

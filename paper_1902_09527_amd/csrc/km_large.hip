@@ -1298,19 +1298,11 @@ hipError_t launch_large_reduce(const Dev& dv, const Large& lg, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The widths the path has taken so far: those whose rows, 16 at a time, fit in
-// LDS as float64 (the table no longer needs it).
-int large_table_lds(int d) { return 128 * d + 16384; }
-
-hipError_t large_set_attributes(int k, int d) {
-    hipError_t e;
-    const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
-    if ((e = hipFuncSetAttribute(large_mfma_symbol(), attr, large_mfma_lds())) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_full_large), attr, 8 * d)) != hipSuccess)
-        return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hist_large), attr, 4 * k)) != hipSuccess)
-        return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_scatter_large), attr, 4 * k);
+const void* large_dynamic_symbol(int i) {
+    const void* const s[kLgDynamic] = {reinterpret_cast<const void*>(&k_full_large),
+                                       reinterpret_cast<const void*>(&k_hist_large),
+                                       reinterpret_cast<const void*>(&k_scatter_large)};
+    return s[i];
 }
 
 hipError_t launch_large_table(const Dev& dv, const Large& lg, int force, hipStream_t s) {

@@ -17,6 +17,7 @@ import synth
 from parity import check_assign, check_centroids
 
 import paper_1902_09527_amd as km
+from paper_1902_09527_amd import _native as N
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -203,3 +204,26 @@ def test_global_path_keeps_every_candidate_of_a_survivor(m):
     assert s1["rechecks"] >= n
     a, _, _ = km.run(Xg, Cg, 1, large_path=True)
     assert int((a % m).max()) == 0
+
+
+def test_open_contexts_of_the_global_path_step_in_turn():
+    # the histogram's LDS is 4 k bytes (80 KB and 1 KB), the full decision's 8 d:
+    # an open context must not lose its limit to one opened later
+    shapes = ((20000, 4, 20000), (2000, 30, 300), (1500, 1152, 257))
+    data = [synth.blobs(n, d, k, seed=891 + d, spread=4.0, sigma=1.5, comps=40) for n, d, k in shapes]
+    want = [km.run(_gpu(X), _gpu(C0), 3, large_path=True) for X, C0 in data]
+    ctxs = [km.KMeansMTI(_gpu(X), _gpu(C0), large_path=True) for X, C0 in data]
+    for t in range(3):
+        for ctx in ctxs:
+            ctx.iterate(sync=True)
+    for ctx, (a, c, _) in zip(ctxs, want):
+        b, e = ctx.get()
+        torch.cuda.synchronize()
+        assert torch.equal(a, b) and torch.equal(c, e)
+        ctx.close()
+
+
+def test_global_path_refuses_wide_rows():
+    X = torch.randn(300, 1153, device=DEV)
+    with pytest.raises(N.KMError, match="d <= 1152"):
+        km.KMeansMTI(X, X[:260].contiguous())
