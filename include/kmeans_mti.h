@@ -25,6 +25,9 @@
  * same inputs are bitwise identical.  Distances run in float32; a point
  * whose best and second-best float32 distances are within the float32 error
  * bound is decided again in float64 against float64 master centroids.
+ * Squared distances that decide have to lie in float32's normal range
+ * (coordinate differences of about 1e-18 to 1e18); the "lds-inc" path takes
+ * smaller data too, in float64.
  *
  * Memory.  X, C0, assign_out and C_out are DEVICE pointers (HIP device
  * memory of the current device).  X is n rows of d contiguous float32

@@ -519,6 +519,7 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
     if (tid == 0) *tcount = 0;
     __syncthreads();
     float cnmax, cbad = 0.f;
+    bool tiny;
     {
         float m2 = 0.f;
         for (int i = lane; i < k; i += 64) {
@@ -532,6 +533,11 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
             cbad = fmaxf(cbad, __shfl_xor(cbad, off));
         }
         cnmax = sqrtf(m2) * kUp * kUp;
+        // Norms this far below 1 have lost bits in cn2 (float32, unscaled) or
+        // all of them, and so have the direct form's distances: every survivor
+        // is decided in float64.
+        tiny = m2 < 0x1p-100f * xsc * xsc;
+        if (tiny) cbad = 1.f;
     }
     const float Dp = (float)(16 * ns);
     const float gexp = (Dp + 8.f) * 0x1p-24f;
@@ -695,6 +701,7 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
             const float band = 2.f * gamma * (d1 + d2) + 4.f * (sqrtf(d1) + sqrtf(d2)) * ecmax + 8.f * ecmax * ecmax;
             re = d2 - d1 <= band;
         }
+        re |= live && tiny;
         // Float64 against the master centroids, every distance summed over the
         // dimensions in order by one lane as on the other paths: rows at equal
         // distances from two centroids then fall alike on all of them.

@@ -227,3 +227,18 @@ def test_global_path_refuses_wide_rows():
     X = torch.randn(300, 1153, device=DEV)
     with pytest.raises(N.KMError, match="d <= 1152"):
         km.KMeansMTI(X, X[:260].contiguous())
+
+
+@pytest.mark.parametrize("d,k", [(24, 40), (70, 20), (5, 129)])
+@pytest.mark.parametrize("scale", [1e-18, 1e-21, 1e-24, 1e-30])
+def test_matrix_core_step_on_data_below_the_range_of_squares(d, k, scale):
+    # |c|^2 is subnormal in float32 from about 1e-19 on and zero from 1e-23 on
+    X, C0 = synth.blobs(3000, d, k, seed=901 + d, spread=4.0, sigma=1.5)
+    X, C0 = X * np.float32(scale), C0 * np.float32(scale)
+    with km.KMeansMTI(_gpu(X), _gpu(C0)) as ctx:
+        assert ctx.path() == "lds-inc"
+    a, c, st = km.run(_gpu(X), _gpu(C0), 8)
+    ref = oracle.lloyd(X, C0, 8)
+    assert st["iterations"] == ref["iters"]
+    check_assign(a.cpu().numpy(), ref["assign"], ref["best"], ref["second"])
+    check_centroids(c.cpu().numpy(), ref["C"], X)
