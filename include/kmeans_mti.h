@@ -321,7 +321,8 @@ int kmeans_pp_run_best(const float* X, int64_t n, int32_t d, int32_t k, const do
  * Release a context.  NULL-safe.  Synchronizes.  Its device buffers are kept
  * by the library (per device and size, at most 8 GiB in all) for the next
  * context that needs the same sizes, so that repeated runs of a problem make
- * no hipMalloc / hipFree calls; kmeans_mti_release_cache frees them.
+ * no hipMalloc / hipFree calls; kmeans_mti_release_cache frees them, and so
+ * does a context on the device that runs out of memory.
  */
 void kmeans_mti_destroy(km_ctx* ctx);
 

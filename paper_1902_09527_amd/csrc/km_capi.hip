@@ -112,6 +112,35 @@ void cache_give(int dev, size_t bytes, void* p) {
     (void)hipFree(p);
 }
 
+// Bytes kept for a device.
+size_t cache_bytes(int dev) {
+    std::lock_guard<std::mutex> lock(g_cache_mu);
+    size_t b = 0;
+    for (int i = 0; i < g_cache_n; ++i)
+        if (g_cache[i].dev == dev) b += g_cache[i].bytes;
+    return b;
+}
+
+// Frees the buffers kept for a device (dev < 0: for all).
+void cache_drop(int dev) {
+    CachedBuf held[kCacheSlots];
+    int m = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_cache_mu);
+        int keep = 0;
+        for (int i = 0; i < g_cache_n; ++i) {
+            if (dev >= 0 && g_cache[i].dev != dev) {
+                g_cache[keep++] = g_cache[i];
+                continue;
+            }
+            held[m++] = g_cache[i];
+            g_cache_bytes -= g_cache[i].bytes;
+        }
+        g_cache_n = keep;
+    }
+    for (int i = 0; i < m; ++i) (void)hipFree(held[i].p);
+}
+
 // Pinned host blocks (256 bytes, coherent: kernels may store to them while
 // the host polls) for a run's progress word and read-backs, reused across
 // runs (hipHostMalloc and hipHostFree cost tens of microseconds each).
@@ -274,6 +303,11 @@ struct km_ctx {
         *q = cache_take(device, bytes);
         if (!*q) {
             hipError_t e = hipMalloc(q, bytes);
+            if (e == hipErrorOutOfMemory) {   // the buffers kept for other sizes may be in the way
+                (void)hipGetLastError();
+                cache_drop(device);
+                e = hipMalloc(q, bytes);
+            }
             if (e != hipSuccess) return hip_fail(e, "hipMalloc");
         }
         buf_bytes[nbufs] = bytes;
@@ -410,19 +444,20 @@ int read_state(km_ctx* c, km::IterState* out) {
 // path: 1M x 10, k = 477 4.82 and 0.33 ms; 157K x 4, k = 593 0.32 and 0.14 ms;
 // 5000 x 6, k = 900 0.39 and 0.07 ms.  The path keeps split rows and candidate
 // lists (64 bytes per 16 dimensions and per 256 centroids, and about 60 more, a
-// row), the general kernel 8 bytes a row: where that is much memory it has to
-// be there twice over.
-bool large_pays(int64_t n, int32_t d, int32_t k) {
+// row), the general kernel 8 bytes a row: it has to be there twice over, so
+// that a problem that fitted on a nearly full device still does.  The buffers
+// the library keeps for this device count as free: they are given back when an
+// allocation fails.
+bool large_pays(int64_t n, int32_t d, int32_t k, int dev) {
     if (k <= km::kGenMatMaxK || d > km::kLgMaxD || k >= 0xffff) return false;
     const double need = (double)n * (64.0 * km::split_chunks(d) + 64.0 * ((k + km::kLgN - 1) / km::kLgN) + 60.0);
     if (n > INT_MAX || need > 64.0 * (1 << 30)) return false;
-    if (need < 1.0 * (1 << 30)) return true;
     size_t avail = 0, total = 0;
     if (hipMemGetInfo(&avail, &total) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return 2.0 * need <= (double)avail;
+    return 2.0 * need <= (double)avail + (double)cache_bytes(dev);
 }
 
 // Set-up of a context.  max_iters / tol_n: the stop rule written into the
@@ -538,11 +573,6 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
         if (want < cus) want = nwt < cus ? nwt : cus;
         c->gg = (int)(G < want ? G : want);
         v.G = 1;
-    } else if (!elkan && !(c->flags & (KM_FLAG_LARGE_PATH | KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY |
-                                         KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE)) &&
-               large_pays(n, d, k)) {
-        // More centroids than the incremental steps take: the global path,
-        // although the general kernel's tables would fit in LDS.
     } else if (!(c->flags & KM_FLAG_LARGE_PATH)) {
         c->variant = km::assign_variant(d, k, aligned, (c->flags & KM_FLAG_VECTOR_ONLY) != 0, elkan);
         const bool h_lds = km::assign_h_lds(c->variant % 16, k);
@@ -554,6 +584,12 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
                 c->lds = bytes;
             }
         }
+        // More centroids than the incremental steps take: the global path,
+        // although the general kernel's tables fit in LDS.
+        if (c->tp > 0 && !elkan &&
+            !(c->flags & (KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY | KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE)) &&
+            large_pays(n, d, k, c->device))
+            c->tp = 0;
     }
     if (c->small || c->gen) {
         // configured above
@@ -1308,17 +1344,7 @@ const char* kmeans_mti_path(const km_ctx* ctx) {
 
 void kmeans_mti_destroy(km_ctx* ctx) { delete ctx; }
 
-void kmeans_mti_release_cache(void) {
-    CachedBuf held[kCacheSlots];
-    int m = 0;
-    {
-        std::lock_guard<std::mutex> lock(g_cache_mu);
-        for (int i = 0; i < g_cache_n; ++i) held[m++] = g_cache[i];
-        g_cache_n = 0;
-        g_cache_bytes = 0;
-    }
-    for (int i = 0; i < m; ++i) (void)hipFree(held[i].p);
-}
+void kmeans_mti_release_cache(void) { cache_drop(-1); }
 
 const char* kmeans_mti_strerror(int status) {
     switch (status) {

@@ -242,3 +242,55 @@ def test_matrix_core_step_on_data_below_the_range_of_squares(d, k, scale):
     assert st["iterations"] == ref["iters"]
     check_assign(a.cpu().numpy(), ref["assign"], ref["best"], ref["second"])
     check_centroids(c.cpu().numpy(), ref["C"], X)
+
+
+@pytest.fixture
+def leave_free():
+    # fills the device up to the given number of free bytes
+    held = []
+
+    def fill(target):
+        torch.cuda.empty_cache()
+        km.kmeans.release_cache()
+        while True:
+            free = torch.cuda.mem_get_info()[0]
+            if free - target < (32 << 20):
+                return
+            held.append(torch.empty(min(free - target, 16 << 30), dtype=torch.uint8, device=DEV))
+    yield fill
+    held.clear()
+    torch.cuda.empty_cache()
+    km.kmeans.release_cache()
+
+
+def _path(X, C0, **kw):
+    with km.KMeansMTI(X, C0, **kw) as ctx:
+        ctx.iterate(sync=True)
+        return ctx.path()
+
+
+def test_route_of_many_centroids_follows_the_free_memory(leave_free):
+    # 252 bytes a row on the global path, 8 on the general kernel
+    g = torch.Generator(device=DEV)
+    g.manual_seed(911)
+    X = torch.randn(5_200_000, 2, generator=g, device=DEV)
+    C0 = X[:300].contiguous()
+    small = X[:3_500_000]
+    want = km.run(small, C0, 2)
+    torch.cuda.synchronize()
+    leave_free(1536 << 20)
+    assert _path(small, C0) == "lds-vector"        # needs 0.82 GiB, 1.5 free: not twice that
+    got = km.run(small, C0, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+
+
+def test_kept_buffers_count_as_free_memory(leave_free):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(912)
+    X = torch.randn(9_000_000, 2, generator=g, device=DEV)
+    C0 = X[:300].contiguous()
+    leave_free(3072 << 20)
+    first = _path(X[:5_200_000], C0)               # 1.22 GiB; its buffers are kept
+    assert first == "global-mfma" and _path(X[:5_200_000], C0) == first
+    assert _path(X, C0, large_path=True) == "global-mfma"   # 2.1 GiB: only where those are given back
