@@ -653,7 +653,44 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
             const int j = (int)(wl->pl[o0 + i] & 255u);
             take(wl->pd[o0 + i], j == inc ? -1 : j, j);
         }
-        for (uint64_t am = __ballot(live && tot == 0); am; am &= am - 1) {   // all centroids, a group of lanes each
+        uint64_t am = __ballot(live && tot == 0);   // all centroids
+        if constexpr (ONE) {
+            // Many narrow rows: a lane each, four centroids at a time, as the
+            // general kernel scans.  With duplicate centroids these are most
+            // survivors, and one after another they took 10 times its step:
+            // 500K x 1 whole numbers, k = 128 1130 us a step, now 78 (84 there).
+            // The scan takes as long for one row as for all, a row by groups
+            // of lanes its own time: they meet near this many rows (1 to 10
+            // dimensions, 65 to 256 centroids; with a quarter of them 5000 x 1,
+            // k = 200 took 1.33 times as long, 20K x 6, k = 200 1.41 times).
+            if (d <= kGenLaneD && __popcll(am) > 4 + k * (d + 10) / 100) {
+                const float* xr = P.X + (int64_t)p * d;
+                float x[kGenLaneD];
+#pragma unroll
+                for (int m = 0; m < kGenLaneD; ++m) x[m] = m < d ? xr[m] : 0.f;   // uniform
+                for (int j0 = 0; j0 < k; j0 += 4) {
+                    float a[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float* c = P.C32 + (int64_t)min(j0 + q, k - 1) * d;
+                        a[q] = 0.f;
+#pragma unroll
+                        for (int m = 0; m < kGenLaneD; ++m) {
+                            if (m >= d) break;   // uniform
+                            const float t = x[m] - c[m];
+                            a[q] = fmaf(t, t, a[q]);
+                        }
+                    }
+                    if (live && tot == 0) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (j0 + q < k) take(a[q], j0 + q == inc ? -1 : j0 + q, j0 + q);
+                    }
+                }
+                am = 0;
+            }
+        }
+        for (; am; am &= am - 1) {   // a group of lanes per centroid
             const int l = __builtin_ctzll(am);
             const int pa = __shfl(p, l), ia = __shfl(inc, l);
             float a1 = INFINITY, a2 = INFINITY;

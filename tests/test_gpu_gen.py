@@ -294,3 +294,15 @@ def test_kept_buffers_count_as_free_memory(leave_free):
     first = _path(X[:5_200_000], C0)               # 1.22 GiB; its buffers are kept
     assert first == "global-mfma" and _path(X[:5_200_000], C0) == first
     assert _path(X, C0, large_path=True) == "global-mfma"   # 2.1 GiB: only where those are given back
+
+
+@pytest.mark.parametrize("d", [1, 3, 16])
+@pytest.mark.parametrize("k,distinct", [(65, 5), (128, 60), (200, 20), (256, 8)])
+def test_many_candidates_of_duplicate_rows(d, k, distinct):
+    # few distinct rows, so that centroids repeat: more candidates than a
+    # survivor keeps, for many survivors of a batch or few
+    rng = np.random.default_rng(921 + d + k)
+    rows = rng.normal(0.0, 3.0, (distinct, d)).astype(np.float32)
+    X = rows[rng.integers(0, distinct, 5001)]
+    X[::97] += np.float32(0.25)
+    _same(_gpu(X), _gpu(X[rng.permutation(5001)[:k]]), 6)
