@@ -124,6 +124,8 @@ struct FullPart {
 constexpr int kMultiCand = 6;        // candidates kept with a survivor (16 bits each; k < 65535)
 constexpr int kFullCap = 4096;       // survivors per step whose decision is split over blocks
 constexpr int kFullSplit = 8;        // blocks (centroid ranges) per split decision
+constexpr int kFullLaneD = 16;       // a lane per decision up to this d ...
+constexpr int kFullLaneRows = 8;     // ... and from this many survivors per centroid on
 
 struct Large {
     int32_t* surv;        // n: survivor point indices of the current step

@@ -563,7 +563,7 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
     const float ecm = st->ec_max;
     const float gexp = (float)(d + 8) * 0x1p-24f;
     const float gsp2 = 2.f * (778.f + 6.9f * (float)(16 * Lg.nch)) * 0x1p-24f * (1.f + 0x1p-10f);
-    uint64_t my_changed = 0, my_comp = 0, my_rc = 0;
+    uint64_t my_changed = 0, my_comp = 0;
     // A group of lps lanes (a power of two, 2 nct or more up to 64) shares a
     // survivor, a lane per two candidate lists: one coalesced read of its
     // keys.
@@ -709,7 +709,6 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
         if (lead) my_comp += (uint64_t)k;
         if (full && lead) {
             Lg.fq[atomicAdd(Lg.nfull, 1u)] = (int32_t)c;
-            my_rc += 1;
         }
         int b = -1;
         if (live && single) {   // from the lane that holds it
@@ -761,9 +760,9 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
     flush(true);
     {
         const int base = k * d + k;
-        const int slot[3] = {base + kStChanged, base + kStComputed, base + kStRecheck};
-        uint64_t v[3] = {my_changed, my_comp, my_rc};
-        add_stats_block<3>(P.total, slot, v);
+        const int slot[2] = {base + kStChanged, base + kStComputed};
+        uint64_t v[2] = {my_changed, my_comp};
+        add_stats_block<2>(P.total, slot, v);
     }
 }
 
@@ -911,7 +910,7 @@ __global__ __launch_bounds__(256) void k_multi_large(Dev P, Large Lg) {
 }
 
 // ---------------------------------------------------------------------------
-// Float64 decision over all centroids for the queued survivors.  The first
+// Decision over all centroids for the queued survivors, in float64.  The first
 // kFullCap of them are split over kFullSplit blocks, each taking a range of
 // centroids (the row in LDS as float64, one centroid per thread, its
 // distance summed over the dimensions in order) and writing its best under
@@ -919,6 +918,15 @@ __global__ __launch_bounds__(256) void k_multi_large(Dev P, Large Lg) {
 // index); the block that finishes a survivor last (a counter per survivor
 // behind a fence) combines the ranges and writes the decision.  Survivors
 // past kFullCap take one block over all centroids.
+//
+// Many narrow rows (d <= kFullLaneD, more than kFullLaneRows k of them) take a lane
+// each: the direct float32 form over all centroids, as the general kernel
+// scans, and float64 only for the near ties.  Duplicate centroids and centroids
+// closer than the split products tell apart send most survivors here: 50K x 1,
+// k = 500 took 813 us a step with a block each, 280 with a lane each (196 on the
+// general kernel).  A block per row costs about 2 us of one of 1024 blocks, the
+// scan about 0.1 us a centroid however many rows there are: 8 rows per centroid
+// is where a split row's 8 blocks and the scan take as long.
 
 __global__ __launch_bounds__(256) void k_full_large(Dev P, Large Lg) {
     IterState* st = P.st;
@@ -948,6 +956,86 @@ __global__ __launch_bounds__(256) void k_full_large(Dev P, Large Lg) {
         }
         P.u[i] = f32_up(sqrt(D) * (1.0 + 0x1p-40));
     };
+    if (d <= kFullLaneD && nf > (uint32_t)(kFullLaneRows * k)) {
+        const float gamma = P.gamma, ecm = st->ec_max;
+        uint64_t my_rc = 0;
+        for (uint32_t q = blockIdx.x * blockDim.x + tid; q < nf; q += gridDim.x * blockDim.x) {
+            const int64_t i = Lg.surv[Lg.fq[q]];
+            const int inc = first ? -1 : P.a[i];
+            const float* xr = P.X + i * d;
+            float x[kFullLaneD];
+#pragma unroll
+            for (int m = 0; m < kFullLaneD; ++m) x[m] = m < d ? xr[m] : 0.f;   // uniform
+            float d1 = INFINITY, d2 = INFINITY;
+            int rk1 = INT_MAX, b = 0;
+            for (int j0 = 0; j0 < k; j0 += 4) {
+                float a[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float* c = P.C32 + (int64_t)min(j0 + e, k - 1) * d;
+                    a[e] = 0.f;
+#pragma unroll
+                    for (int m = 0; m < kFullLaneD; ++m) {
+                        if (m >= d) break;   // uniform
+                        const float t = x[m] - c[m];
+                        a[e] = fmaf(t, t, a[e]);
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int j = j0 + e, rk = j == inc ? -1 : j;
+                    if (j >= k) continue;
+                    if (a[e] < d1 || (a[e] == d1 && rk < rk1)) {
+                        d2 = d1;
+                        d1 = a[e];
+                        rk1 = rk;
+                        b = j;
+                    } else if (a[e] < d2) {
+                        d2 = a[e];
+                    }
+                }
+            }
+            // Float64 for near ties, and where float32 squares overflow or lose
+            // bits; a distance below 2^-50 alone is bounded by 2^-49.
+            float ub = upper_bound(d1, P.ec[b], gamma);
+            if (d1 < 0x1p-100f) ub = fmaxf(ub, 0x1p-49f);
+            const float band = 2.f * gamma * (d1 + d2) + 4.f * (sqrtf(d1) + sqrtf(d2)) * ecm + 8.f * ecm * ecm;
+            if (!(d2 - d1 > band) || !(d2 <= 0x1p120f) || (d1 < 0x1p-100f && d2 < 0x1p-96f)) {
+                double Db = INFINITY;
+                int kb = INT_MAX, bb = 0;
+                for (int j = 0; j < k; ++j) {
+                    const double D = sqd64(xr, P.C64 + (int64_t)j * d, d);
+                    const int rk = j == inc ? -1 : j;
+                    if (D < Db || (D == Db && rk < kb)) {
+                        Db = D;
+                        kb = rk;
+                        bb = j;
+                    }
+                }
+                b = bb;
+                ub = f32_up(sqrt(Db) * (1.0 + 0x1p-40));
+                my_rc += 1;
+            }
+            if (b != inc) {
+                P.a[i] = b;
+                my_changed += 1;
+                if (rec_moves) {
+                    const uint32_t qm = atomicAdd(Lg.nmv, 1u);
+                    if (qm < (uint32_t)Lg.mvcap) Lg.mv[qm] = make_int4((int)i, inc, b, 0);
+                }
+            }
+            P.u[i] = ub;
+        }
+        const int base = k * d + k;
+        const int slot[2] = {base + kStChanged, base + kStRecheck};
+        uint64_t v[2] = {my_changed, my_rc};
+        add_stats_block<2>(P.total, slot, v);
+        return;
+    }
+    if (blockIdx.x == 0 && tid == 0 && nf) {   // every survivor below is decided in float64
+        unsigned long long* sc = reinterpret_cast<unsigned long long*>(P.total + (int64_t)k * d + k);
+        atomicAdd(&sc[kStRecheck], (unsigned long long)nf);
+    }
     const uint32_t items = nsplit * kFullSplit + (nf - nsplit);
     for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
         const bool split = it < nsplit * kFullSplit;

@@ -297,12 +297,20 @@ def test_kept_buffers_count_as_free_memory(leave_free):
 
 
 @pytest.mark.parametrize("d", [1, 3, 16])
-@pytest.mark.parametrize("k,distinct", [(65, 5), (128, 60), (200, 20), (256, 8)])
+@pytest.mark.parametrize("k,distinct", [(65, 5), (128, 60), (200, 20), (256, 8), (300, 30), (700, 60)])
 def test_many_candidates_of_duplicate_rows(d, k, distinct):
     # few distinct rows, so that centroids repeat: more candidates than a
-    # survivor keeps, for many survivors of a batch or few
+    # survivor keeps, for many survivors of a batch or few (k <= 256); on the
+    # global path 5001 survivors are more than 8 k at k = 300 and fewer at 700
     rng = np.random.default_rng(921 + d + k)
     rows = rng.normal(0.0, 3.0, (distinct, d)).astype(np.float32)
     X = rows[rng.integers(0, distinct, 5001)]
     X[::97] += np.float32(0.25)
-    _same(_gpu(X), _gpu(X[rng.permutation(5001)[:k]]), 6)
+    C0 = X[rng.permutation(5001)[:k]]
+    _same(_gpu(X), _gpu(C0), 6)
+    if k > 256:
+        for scale in (1e-24, 1.0, 1e24):     # float32 squares vanish, hold, overflow
+            a, c, _ = km.run(_gpu(X * np.float32(scale)), _gpu(C0 * np.float32(scale)), 6, large_path=True)
+            ref = oracle.lloyd(X * np.float32(scale), C0 * np.float32(scale), 6)
+            check_assign(a.cpu().numpy(), ref["assign"], ref["best"], ref["second"])
+            check_centroids(c.cpu().numpy(), ref["C"], X * np.float32(scale))
