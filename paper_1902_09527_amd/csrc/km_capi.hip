@@ -447,9 +447,12 @@ int read_state(km_ctx* c, km::IterState* out) {
 // row), the general kernel 8 bytes a row: it has to be there twice over, so
 // that a problem that fitted on a nearly full device still does.  The buffers
 // the library keeps for this device count as free: they are given back when an
-// allocation fails.
+// allocation fails.  One column stays with the general kernel: hundreds of
+// centroids on a line lie closer than the split products tell apart, so that
+// most survivors have many candidates (50K x 1, k = 500 196 us a step there, 280
+// on the global path; 500K x 1, k = 300 200 and 532).
 bool large_pays(int64_t n, int32_t d, int32_t k, int dev) {
-    if (k <= km::kGenMatMaxK || d > km::kLgMaxD || k >= 0xffff) return false;
+    if (k <= km::kGenMatMaxK || d < 2 || d > km::kLgMaxD || k >= 0xffff) return false;
     const double need = (double)n * (64.0 * km::split_chunks(d) + 64.0 * ((k + km::kLgN - 1) / km::kLgN) + 60.0);
     if (n > INT_MAX || need > 64.0 * (1 << 30)) return false;
     size_t avail = 0, total = 0;

@@ -44,7 +44,7 @@ CASES = [
     (4097, 15, 32, "lds-inc"), (4096, 17, 33, "lds-inc"), (300000 + 7, 20, 64, "lds-inc"),
     (3001, 31, 65, "lds-inc"), (3000, 33, 100, "lds-inc"), (6000, 48, 128, "lds-inc"),
     (2500, 63, 30, "lds-inc"), (2500, 64, 31, "lds-inc"), (2500, 65, 40, "lds-inc"),
-    (4000, 5, 129, "lds-inc"), (4001, 9, 256, "lds-inc"), (3000, 5, 257, "global-mfma"),
+    (4000, 5, 129, "lds-inc"), (4001, 9, 256, "lds-inc"), (3000, 5, 257, "global-mfma"), (3000, 1, 257, "lds-vector"),
     (1500, 129, 33, "lds-inc"), (1201, 255, 20, "lds-inc"), (900, 600, 9, "lds-inc"),
 ]
 
