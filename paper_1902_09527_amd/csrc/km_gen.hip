@@ -1270,14 +1270,14 @@ __global__ __launch_bounds__(kFinThreads) void k_gen_finish(Dev P_) {
 
 static int gen_finish_lds(int d, int k) { return k * (d | 1) * 24 + k * 12 + 64 + 16; }
 
-// One block against two launches of k blocks, whole runs at 3000 rows, two
-// launches and one block: d x k = 20 x 20 (k k d = 8000) 373 and 315 us for 12
-// steps, 8 x 64 (32768) 395 and 372; for 6 steps 14 x 50 (35000) 229 and 245,
-// 20 x 40 (32000) 235 and 250, 2 x 90 (16200) 239 and 268, 2 x 181 (65522) 284 and
-// 413.  The table's k^2 d differences and the k d coordinates' 18 words each are
-// what one block has to do; past 64 rows its 32 groups of lanes take a third
-// round of them.
-bool gen_finish_applies(int d, int k) { return k <= 64 && k * d <= 1024 && k * k * d <= (k * d <= 512 ? 32768 : 16384); }
+// One block against two launches of k blocks, whole runs, two launches and one
+// block: 12 steps of 3000 x 20, k = 20 (k k d = 8000) 373 and 315 us, of 395 x 27, k =
+// 31 (25947) 371 and 335, of 3000 x 8, k = 64 (32768) 395 and 372; 6 steps of 3000
+// x 20, k = 40 (32000) 235 and 250, x 14, k = 50 (35000) 229 and 245, x 2, k = 90
+// (16200) 239 and 268, x 2, k = 181 (65522) 284 and 413.  The table's k^2 d
+// differences and the k d coordinates' 18 words each are what one block has to
+// do; past 64 rows its 32 groups of lanes take a third round of them.
+bool gen_finish_applies(int d, int k) { return k <= 64 && k * d <= 1024 && k * k * d <= (k * d <= 512 ? 32768 : 28000); }
 
 hipError_t launch_gen_finish(const Dev& dv, hipStream_t s) {
     hipLaunchKernelGGL(k_gen_finish, dim3(1), dim3(kFinThreads), gen_finish_lds(dv.d, dv.k), s, dv);
