@@ -438,21 +438,31 @@ int read_state(km_ctx* c, km::IterState* out) {
     return KM_OK;
 }
 
-// Whether a problem whose centroids would fit in LDS goes to the global path:
-// from k = 257 on, where only the general kernel (every row read, one scalar
-// scan per survivor) is left beside it.  Per step, general kernel and global
+// Whether a problem that the general kernel (every row read, one scalar scan per
+// survivor) could take goes to the global path: from k = 257 on.  (Fewer
+// centroids whose tables are too large for the incremental step's LDS, 65 to 82
+// at d = 128, stay with the general kernel.)  Per step, general kernel and global
 // path: 1M x 10, k = 477 4.82 and 0.33 ms; 157K x 4, k = 593 0.32 and 0.14 ms;
 // 5000 x 6, k = 900 0.39 and 0.07 ms.  The path keeps split rows and candidate
 // lists (64 bytes per 16 dimensions and per 256 centroids, and about 60 more, a
 // row), the general kernel 8 bytes a row: it has to be there twice over, so
 // that a problem that fitted on a nearly full device still does.  The buffers
 // the library keeps for this device count as free: they are given back when an
-// allocation fails.  One column stays with the general kernel: hundreds of
-// centroids on a line lie closer than the split products tell apart, so that
-// most survivors have many candidates (50K x 1, k = 500 196 us a step there, 280
-// on the global path; 500K x 1, k = 300 200 and 532).
+// allocation fails.  Two kinds of problem stay with the general kernel (20K x 2,
+// k = 300, where it has too few waves, 118 us a step there and 84 on the global
+// path):
+//   - one column with more than 10 rows a centroid: hundreds of centroids on a
+//     line lie closer than the split products tell apart, so that most
+//     survivors have many candidates (50K x 1, k = 500 196 us a step there, 280 on
+//     the global path; 2716 x 1, k = 282 101 and 81);
+//   - many rows of few dimensions and not many more than 256 centroids: its
+//     scan, about k (2 d + 8) instructions a survivor, costs no more than the
+//     candidate lists (200K x 2, k = 260 145 and 222 us, 200K x 3, k = 260 173 and
+//     200; 200K x 4, k = 260 229 and 214, 200K x 3, k = 400 239 and 191).
 bool large_pays(int64_t n, int32_t d, int32_t k, int dev) {
-    if (k <= km::kGenMatMaxK || d < 2 || d > km::kLgMaxD || k >= 0xffff) return false;
+    if (k <= km::kGenMatMaxK || d > km::kLgMaxD || k >= 0xffff) return false;
+    if (d == 1 && n > 10 * (int64_t)k) return false;
+    if (n > 100000 && (int64_t)k * (2 * d + 8) < 4000) return false;
     const double need = (double)n * (64.0 * km::split_chunks(d) + 64.0 * ((k + km::kLgN - 1) / km::kLgN) + 60.0);
     if (n > INT_MAX || need > 64.0 * (1 << 30)) return false;
     size_t avail = 0, total = 0;

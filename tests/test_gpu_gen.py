@@ -45,6 +45,7 @@ CASES = [
     (3001, 31, 65, "lds-inc"), (3000, 33, 100, "lds-inc"), (6000, 48, 128, "lds-inc"),
     (2500, 63, 30, "lds-inc"), (2500, 64, 31, "lds-inc"), (2500, 65, 40, "lds-inc"),
     (4000, 5, 129, "lds-inc"), (4001, 9, 256, "lds-inc"), (3000, 5, 257, "global-mfma"), (3000, 1, 257, "lds-vector"),
+    (2000, 1, 257, "global-mfma"), (100001, 2, 260, "lds-vector"), (100001, 4, 260, "global-mfma"),
     (1500, 129, 33, "lds-inc"), (1201, 255, 20, "lds-inc"), (900, 600, 9, "lds-inc"),
 ]
 
@@ -274,7 +275,7 @@ def test_route_of_many_centroids_follows_the_free_memory(leave_free):
     g = torch.Generator(device=DEV)
     g.manual_seed(911)
     X = torch.randn(5_200_000, 2, generator=g, device=DEV)
-    C0 = X[:300].contiguous()
+    C0 = X[:400].contiguous()
     small = X[:3_500_000]
     want = km.run(small, C0, 2)
     torch.cuda.synchronize()
@@ -289,7 +290,7 @@ def test_kept_buffers_count_as_free_memory(leave_free):
     g = torch.Generator(device=DEV)
     g.manual_seed(912)
     X = torch.randn(9_000_000, 2, generator=g, device=DEV)
-    C0 = X[:300].contiguous()
+    C0 = X[:400].contiguous()
     leave_free(3072 << 20)
     first = _path(X[:5_200_000], C0)               # 1.22 GiB; its buffers are kept
     assert first == "global-mfma" and _path(X[:5_200_000], C0) == first
