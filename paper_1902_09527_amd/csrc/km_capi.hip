@@ -391,7 +391,21 @@ int enqueue_iteration(km_ctx* c) {
         c->stepped = true;
         return KM_OK;
     }
-    e = c->gen     ? km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, c->stream)
+    // A first call that is recorded into a graph may be replayed as any step:
+    // both forms are recorded, and the loop state picks one at each replay.
+    int first = c->gen && c->enq == 0 ? 1 : 0, check = 0;
+    if (first) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if ((e = hipStreamIsCapturing(c->stream, &cap)) != hipSuccess)
+            return fail_ctx(c, hip_fail(e, "hipStreamIsCapturing"));
+        if (cap == hipStreamCaptureStatusActive) {
+            e = km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, 1, 1, c->stream);
+            if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "assign kernel"));
+            first = 0;
+            check = 1;
+        }
+    }
+    e = c->gen     ? km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, first, check, c->stream)
         : c->large ? km::launch_large_assign(c->dv, c->lg, c->gb, c->stream)
                    : km::launch_assign(c->dv, c->variant, c->tp, c->lds, c->stream);
     if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "assign kernel"));

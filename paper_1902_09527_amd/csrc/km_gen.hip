@@ -23,6 +23,7 @@
 // the running sums and clears them.
 #include <float.h>
 #include <limits.h>
+#include <stddef.h>
 #include <math.h>
 
 #include "kmeans_mti.h"
@@ -59,6 +60,17 @@ template <int CB>
 __device__ __forceinline__ uint32_t state_of(float ub, float ddn, int b) {
     const float rr = ub - ddn;
     return pack_state<CB>(rr + fabsf(rr) * 0x1p-22f, b);
+}
+
+// Whether a launch has nothing to do: the run has stopped (the step is marked
+// as not running), or the other form of a recorded first step runs.  One load.
+__device__ __forceinline__ bool step_idle(IterState* st, int first, int check) {
+    static_assert(offsetof(IterState, done) == offsetof(IterState, t) + 4, "t and done are one load");
+    const int2 td = *reinterpret_cast<const int2*>(&st->t);
+    const int other = check & ((td.x == 0 ? 1 : 0) ^ first);
+    if (!(td.y | other)) return false;
+    if (td.y && blockIdx.x == 0 && threadIdx.x == 0) st->active = 0;
+    return true;
 }
 
 // LDS ordering point inside one wave.
@@ -141,14 +153,10 @@ __device__ __forceinline__ void flush_block(const Dev& P, const uint64_t* acc, c
 // (the survivors' lines and the states are 0.5 ms at 4.8 TB/s).
 
 template <int DP>
-__global__ __launch_bounds__(kGenThreads) void k_inc_vec(Dev P_, int nsub) {
+__global__ __launch_bounds__(kGenThreads) void k_inc_vec(Dev P_, int first, int check, int nsub) {
     const Dev P = with_scales(P_);
     IterState* st = P.st;
-    const bool first = st->t == 0;   // from the device: a captured step can be replayed as any step
-    if (st->done) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) st->active = 0;
-        return;
-    }
+    if (step_idle(st, first, check)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) st->active = 1;
     const int k = P.k, d = P.d, tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -442,14 +450,10 @@ template <int KB, bool ONE>
 constexpr int gen_mat_steps() { return ONE || KB >= 4 ? 2 : 4; }
 
 template <int KB, bool VEC, bool ONE>
-__global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_waves_per_eu(gen_mat_waves(KB, ONE) / 4))) void k_inc_mat(Dev P_, int nsub) {
+__global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_waves_per_eu(gen_mat_waves(KB, ONE) / 4))) void k_inc_mat(Dev P_, int first, int check, int nsub) {
     const Dev P = with_scales(P_);
     IterState* st = P.st;
-    const bool first = st->t == 0;
-    if (st->done) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) st->active = 0;
-        return;
-    }
+    if (step_idle(st, first, check)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) st->active = 1;
     constexpr int CB = KB == 8 ? 8 : 7;   // cluster bits of a state word
     constexpr int QS = gen_mat_steps<KB, ONE>();
@@ -1344,9 +1348,9 @@ const void* gen_symbol(GenKind kind, const Dev& dv) {
 #undef KM_M
 }
 
-hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, hipStream_t s) {
-#define KM_V(DP_) { hipLaunchKernelGGL(k_inc_vec<DP_>, dim3(grid), dim3(kGenThreads), lds_bytes, s, dv, nsub); }
-#define KM_M(KB_, V_, O_) { hipLaunchKernelGGL((k_inc_mat<KB_, V_, O_>), dim3(grid), dim3(64 * gen_mat_waves(KB_, O_)), lds_bytes, s, dv, nsub); }
+hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, int first, int check, hipStream_t s) {
+#define KM_V(DP_) { hipLaunchKernelGGL(k_inc_vec<DP_>, dim3(grid), dim3(kGenThreads), lds_bytes, s, dv, first, check, nsub); }
+#define KM_M(KB_, V_, O_) { hipLaunchKernelGGL((k_inc_mat<KB_, V_, O_>), dim3(grid), dim3(64 * gen_mat_waves(KB_, O_)), lds_bytes, s, dv, first, check, nsub); }
     KM_GEN_CASES(KM_V, KM_M)
 #undef KM_V
 #undef KM_M

@@ -546,7 +546,10 @@ GenKind gen_kind(int64_t n, int d, int k, int max_lds);
 int gen_lds_bytes(GenKind kind, int d, int k);
 int gen_waves(GenKind kind, int d, int k);   // waves per block
 const void* gen_symbol(GenKind kind, const Dev& dv);
-hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, hipStream_t s);
+// first: 1 for a first step.  check: 1 if the launch does nothing unless the
+// loop state agrees that it is (is not) one.
+hipError_t launch_gen(GenKind kind, const Dev& dv, int grid, int nsub, int lds_bytes, int first, int check,
+                      hipStream_t s);
 // The end of a step in one block (update and centroid table) where k and d are small.
 bool gen_finish_applies(int d, int k);
 hipError_t launch_gen_finish(const Dev& dv, hipStream_t s);
