@@ -743,6 +743,7 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
         zr.add(c->fz.dup, sizeof(float) * (size_t)k);
         zr.add(c->fz.ddn, sizeof(float) * (size_t)k);
     }
+    if ((c->large || c->gen == km::kGenMat) && (rc = c->alloc(&v.mu, (size_t)km::split16(d)))) return rc;
     uint32_t* scratch = nullptr;
     if ((rc = c->alloc(&scratch, 8))) return rc;
     // Inertia (the kernels that read every row sum their own): the squares of
@@ -786,7 +787,7 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
     // status read the set-up back: non-finite input (KM_FLAG_VALIDATE) and a
     // zero C0 row (spherical k-means).
     KM_HIP(km::launch_set_scales(v.st, scratch, n, d, (c->flags & KM_FLAG_SPHERICAL) ? 1 : 0, x2part, nx2, x2sum,
-                                 c->stream));
+                                 (c->flags & KM_FLAG_SPHERICAL) ? v.C32 : C0, k, v.mu, c->stream));
     if (c->flags & (KM_FLAG_VALIDATE | KM_FLAG_SPHERICAL)) {
         uint32_t host[5];
         int32_t* pin = pinned_take();

@@ -403,6 +403,9 @@ __global__ __launch_bounds__(kGenThreads) void k_inc_vec(Dev P_, int first, int 
 // of ordinary values; a row or a centroid table past 2^15 takes the direct
 // form over all centroids.
 //
+// Where the data lie far from the origin, rows and centroids are taken relative
+// to mu (Dev::mu), x 2^a - mu 2^a in one rounding: x and c below are then these.
+//
 // Error of dot' = x.c - |c|^2 / 2 (the nearest centroid has the largest; the
 // row's own norm does not enter the comparison), in scaled units (|x|, |c| of
 // the scaled row and centroid, D = 16 ceil(d / 16)):
@@ -419,6 +422,7 @@ __global__ __launch_bounds__(kGenThreads) void k_inc_vec(Dev P_, int first, int 
 //     centroids in the same component) had several candidates;
 //   - the final additions and the rounded |c|^2: 2 2^-24 |x| |c| and
 //     1.5 2^-24 |c|^2;
+//   - with mu the roundings of x and c, 2.1 2^-24 |x| |c|;
 //   - f16 values below the normal range (flushed at worst): 2^-14 sqrt(D) R,
 //     R = |x| + max |c|.
 // The bound of a settled survivor, from |x|^2 - 2 dot', adds the norm's
@@ -465,6 +469,7 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
     const int col = lane & 31, half = lane >> 5;
     const int ns = (d + 15) / 16;
     const float xsc = st->xscale, xinv = st->xinv;
+    const bool shift = st->shift != 0;
     const float ecmax = st->ec_max, ecs_max = st->ec_max * xsc, gamma = P.gamma;
     const GenMatLds lay = gen_mat_lds(KB, NW, d, k);
     const int AR = lay.ar;
@@ -501,7 +506,14 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
         const int j = cb * 32 + (l & 31), m0 = 16 * s + 8 * (l >> 5);
         float v[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = j < k && m0 + e < d ? P.C32[(int64_t)j * d + m0 + e] * xsc : 0.f;
+        for (int e = 0; e < 8; ++e) v[e] = j < k && m0 + e < d ? P.C32[(int64_t)j * d + m0 + e] : 0.f;
+        if (shift) {   // uniform
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = j < k ? fmaf(v[e], xsc, -(P.mu[m0 + e] * xsc)) : 0.f;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] *= xsc;
+        }
         uint4 hi, lo;
         split8(v, hi, lo);
         cau[((s * KB + cb) * 2) * 64 + l] = hi;
@@ -546,7 +558,7 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
     const float Dp = (float)(16 * ns);
     const float gexp = (Dp + 8.f) * 0x1p-24f;
     const float gacc = kTwo ? 36.3f * (float)min(2, ns) + (float)((ns + 1) / 2) : 6.9f * Dp;
-    const float gsp2 = 2.f * (14.1f + gacc) * 0x1p-24f * (1.f + 0x1p-10f);
+    const float gsp2 = 2.f * (14.1f + (shift ? 2.1f : 0.f) + gacc) * 0x1p-24f * (1.f + 0x1p-10f);
     const float gabs = 0x1p-13f * sqrtf(Dp) * kUp;
 
     uint32_t my_changed = 0, my_comp = 0, my_rc = 0, c1w = 0;
@@ -891,6 +903,11 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
                         v[4 * c + 2] = t.z * xsc;
                         v[4 * c + 3] = t.w * xsc;
                     }
+                    if (shift && (q == 0 || both)) {   // uniform
+                        const float* mp = P.mu + 16 * (s0 + i + q) + 8 * half;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) v[e] = fmaf(A.v[2 * (i + q) + e / 4][e % 4], xsc, -(mp[e] * xsc));
+                    }
                     if (q == 0 || both) {
 #pragma unroll
                         for (int e = 0; e < 8; ++e) x2 = fmaf(v[e], v[e], x2);
@@ -1129,6 +1146,7 @@ __global__ __launch_bounds__(kFinThreads) void k_gen_finish(Dev P_) {
     uint64_t tv0 = P.sums[e0] + row_sum(e0);
     const double cold0 = P.C64[e0];
     const uint64_t cv0 = row_sum(kd + a0) + (a0 < k ? P.sums[kd + a0] : 0);
+    const bool shift = st->shift != 0;
     if (!st->active) return;
     for (int i = tid; i < k + kNumStat; i += kFinThreads) {   // counts, then the counters
         const uint64_t v = i == tid ? cv0 : row_sum(kd + i) + (i < k ? P.sums[kd + i] : 0);
@@ -1191,6 +1209,13 @@ __global__ __launch_bounds__(kFinThreads) void k_gen_finish(Dev P_) {
                 c[m] = cnew;
                 P.C64[j * d + m] = cnew;
                 P.C32[j * d + m] = c32;
+            }
+        }
+        if (shift) {
+            n2 = 0.0;
+            for (int m = g8; m < d; m += 8) {
+                const double v = (double)(float)(keep ? o[m] : c[m]) - (double)P.mu[m];
+                n2 = fma(v, v, n2);
             }
         }
         dr = sum8(dr);

@@ -47,6 +47,8 @@ struct IterState {
     // Scale 2^a of the f16 operands and 2^-a (k_set_scales): the sample's
     // bound on |x| and the largest |c| of C0 map to at most 2^13.
     float xscale, xinv;
+    int32_t shift;        // 1 if Dev::mu is not zero (k_set_scales)
+    int32_t pad3_;
     // Nullable: a pinned, coherent host word that the end of every step sets
     // to the steps ended, negated once the stop test is met (a run's host
     // loop polls it instead of copying the flag).
@@ -66,7 +68,12 @@ struct Dev {
     float* h;             // k*k: half centroid distances rounded down (null on the global path)
     float* s;             // k: min_{j != i} h[i][j] rounded down (+inf if k == 1)
     float* f;             // k: drift ||c_j^t - c_j^{t-1}|| rounded up
-    float* cn2;           // k: ||c32_j||^2 (matrix-core path)
+    float* cn2;           // k: ||c32_j - mu||^2 (matrix-core paths)
+    // Matrix-core form of the incremental steps and global path: a vector that
+    // rows and centroids are taken relative to before their products (split16(d)
+    // floats, zero past d; all zero unless the data lie far from the origin,
+    // k_set_scales), else null.
+    float* mu;
     float* lb;            // Elkan only: k x n lower bounds (centroid-major), offset by the cumulative drift
     double* dhi;          // Elkan and incremental path: k cumulative drifts, rounded up (else null)
     double* dlo;          // Elkan and incremental path: k cumulative drifts, rounded down
@@ -89,6 +96,8 @@ struct Dev {
     float gamma;          // relative error bound of a float32 squared distance, d-dependent
     uint32_t flags;
 };
+
+__host__ __device__ inline int split16(int d) { return (d + 15) / 16 * 16; }
 
 inline int row_len(int d, int k) { return k * d + k + kNumStat; }
 
@@ -428,9 +437,11 @@ struct ZeroRanges {
 hipError_t launch_init_buffers(const ZeroRanges& z, int cus, hipStream_t s);
 // Fixed-point scales into st from the largest |x| and |c0| (float bits in
 // absmax[0] and absmax[2]; unit = 1: spherical k-means, centroids of norm 1).
-// x2part (nullable): nx2 pairs summed into x2sum.
+// x2part (nullable): nx2 pairs summed into x2sum.  mu (nullable): receives the
+// shift of the matrix-core products, from the k centroids at c.
 hipError_t launch_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d, int unit,
-                             const double* x2part, int nx2, double* x2sum, hipStream_t s);
+                             const double* x2part, int nx2, double* x2sum, const float* c, int32_t k, float* mu,
+                             hipStream_t s);
 hipError_t launch_set_centroids(const float* C0, double* C64, float* C32, float* ec, int64_t kd,
                                 int32_t k, hipStream_t s);
 // Spherical k-means: rows of X projected to the unit sphere into Xn; unit

@@ -217,9 +217,80 @@ __global__ __launch_bounds__(256) void k_init_buffers(ZeroRanges z) {
 // those of the sample's bound, and the end of the first step sets them again
 // from the word that step wrote (its sums corrected first when X exceeded
 // the bound).
-__global__ __launch_bounds__(64) void k_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d,
-                                                   int unit, const double* x2part, int nx2, double* x2sum) {
-    if (x2part) {
+//
+// With mu also the shift of the matrix-core products: the mean of the centroids
+// at c (of a few of them) if its norm is more than
+// twice their root mean square distance from it, else zero.  The expanded
+// form's error grows with |x| |c|: relative to the mean it grows with the spread
+// of the data alone (300K x 3, k = 300 at a spread of 4 and an offset of 360 had
+// every row decided over all centroids).  Any vector is exact enough, as long
+// as rows and centroids use the same one.
+constexpr int kShiftRows = 16;   // centroids looked at, in one pass
+
+__global__ __launch_bounds__(256) void k_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d,
+                                                    int unit, const double* x2part, int nx2, double* x2sum,
+                                                    const float* __restrict__ c, int32_t k, float* __restrict__ mu) {
+    const int tid = threadIdx.x;
+    bool shift = false;
+    double dev = 0.0;   // largest |c - mu| of a coordinate
+    if (mu) {
+        __shared__ double ps[256], pq[256];
+        __shared__ float lo[256], hi[256];
+        const int rows = min(k, kShiftRows);
+        int W = 1;   // columns side by side; 256 / W groups of threads share the rows
+        while (W < d && W < 256) W *= 2;
+        const int G = 256 / W, g = tid / W;
+        double far = 0.0;   // |mu|^2 - 4 (mean squared distance from mu), summed over the columns
+        for (int m0 = 0; m0 < d; m0 += W) {
+            const int m = m0 + (tid & (W - 1));
+            double s = 0.0, q = 0.0;
+            float a = INFINITY, b = -INFINITY;
+            if (m < d) {
+#pragma unroll 4
+                for (int r = g; r < rows; r += G) {
+                    const float v = c[(int64_t)r * k / rows * d + m];
+                    s += (double)v;
+                    q += (double)v * (double)v;
+                    a = fminf(a, v);
+                    b = fmaxf(b, v);
+                }
+            }
+            ps[tid] = s;
+            pq[tid] = q;
+            lo[tid] = a;
+            hi[tid] = b;
+            __syncthreads();
+            if (g == 0 && m < d) {
+                for (int h = 1; h < G; ++h) {
+                    s += ps[h * W + tid];
+                    q += pq[h * W + tid];
+                    a = fminf(a, lo[h * W + tid]);
+                    b = fmaxf(b, hi[h * W + tid]);
+                }
+                const float v = (float)(s / rows);
+                mu[m] = v;
+                far += (double)v * (double)v - 4.0 * (q / rows - (double)v * (double)v);
+                dev = fmax(dev, fmax((double)b - (double)v, (double)v - (double)a));
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            far += __shfl_xor(far, o);
+            dev = fmax(dev, __shfl_xor(dev, o));
+        }
+        if ((tid & 63) == 0) {
+            ps[tid >> 6] = far;
+            pq[tid >> 6] = dev;
+        }
+        __syncthreads();
+        far = ps[0] + ps[1] + ps[2] + ps[3];
+        dev = fmax(fmax(pq[0], pq[1]), fmax(pq[2], pq[3]));
+        shift = far > 0.0 && far < INFINITY && dev > 0.0 && dev < FLT_MAX;   // the same in every thread
+        for (int m = tid; m < split16(d); m += 256)   // a thread's own columns, and the padding
+            if (!shift || m >= d) mu[m] = 0.f;
+    }
+    if (x2part && tid < 64) {
         DD s{};
         for (int i = threadIdx.x; i < nx2; i += 64) s = dd_add(s, DD{x2part[2 * i], x2part[2 * i + 1]});
         s = dd_wave_sum(s);
@@ -232,10 +303,11 @@ __global__ __launch_bounds__(64) void k_set_scales(IterState* st, const uint32_t
     const float cmax = unit ? 1.0f : __uint_as_float(absmax[kAmaxC]);
     put_scales(st, sum_exp(absmax), cmax, n, d);
     const int es = bound_exp((double)__uint_as_float(absmax[kAmaxSample])) + 4, ec = bound_exp((double)cmax);
-    int a = 13 - (es > ec ? es : ec);
+    int a = 13 - (shift ? bound_exp(dev) + 6 : es > ec ? es : ec);
     a = a > 100 ? 100 : (a < -100 ? -100 : a);
     st->xscale = ldexpf(1.f, a);
     st->xinv = ldexpf(1.f, -a);
+    st->shift = shift ? 1 : 0;
 }
 
 __global__ void k_set_centroids(const float* __restrict__ C0, double* C64, float* C32, float* ec,
@@ -374,6 +446,13 @@ __global__ __launch_bounds__(256) void k_centroid_table(Dev P, int force) {
         const float* c = P.C32 + (int64_t)i * d;
         double n2 = 0.0;
         for (int m = lane; m < d; m += 64) n2 = fma((double)c[m], (double)c[m], n2);
+        if (P.st->shift) {
+            n2 = 0.0;
+            for (int m = lane; m < d; m += 64) {
+                const double v = (double)c[m] - (double)P.mu[m];
+                n2 = fma(v, v, n2);
+            }
+        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
         if (lane == 0) P.cn2[i] = (float)n2;
@@ -1439,8 +1518,9 @@ hipError_t launch_absmax(const float* a, int64_t na, const float* b, int64_t nb,
 }
 
 hipError_t launch_set_scales(IterState* st, const uint32_t* absmax, int64_t n, int32_t d, int unit,
-                             const double* x2part, int nx2, double* x2sum, hipStream_t s) {
-    hipLaunchKernelGGL(k_set_scales, dim3(1), dim3(64), 0, s, st, absmax, n, d, unit, x2part, nx2, x2sum);
+                             const double* x2part, int nx2, double* x2sum, const float* c, int32_t k, float* mu,
+                             hipStream_t s) {
+    hipLaunchKernelGGL(k_set_scales, dim3(1), dim3(256), 0, s, st, absmax, n, d, unit, x2part, nx2, x2sum, c, k, mu);
     return hipGetLastError();
 }
 

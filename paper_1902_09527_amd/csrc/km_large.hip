@@ -148,8 +148,9 @@ __global__ __launch_bounds__(kLgBoundThreads) void k_bound_large(Dev P, Large Lg
 }
 
 // ---------------------------------------------------------------------------
-// Split rows: hi = bf16(x), lo = bf16(x - hi) (both rounded to nearest; x - hi
-// is exact in float32), in the chunk layout of the matrix-core operands, and
+// Split rows of x = row - mu (rounded to float32; mu is zero unless the data lie
+// far from the origin): hi = bf16(x), lo = bf16(x - hi) (both rounded to
+// nearest; x - hi is exact in float32), in the chunk layout of the matrix-core operands, and
 // the float32 squared norm of every row (each lane sums its dimensions in
 // order, then a fixed butterfly over the wave: deterministic).  Rows from
 // valid to rows are padding: zero operands, norm +inf.  One wave per row.
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(kLgBoundThreads) void k_bound_large(Dev P, Large Lg
 __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ src, int64_t rows, int64_t valid, int d,
                                                     int nch, uint32_t* __restrict__ dst, float* __restrict__ norms,
                                                     const IterState* st, int force, const float* __restrict__ smin,
-                                                    float* __restrict__ s_out) {
+                                                    float* __restrict__ s_out, const float* __restrict__ mu) {
     if (st && !force && !st->active) return;
     const int lane = threadIdx.x & 63;
     const int64_t wstride = (int64_t)gridDim.x * (blockDim.x >> 6);
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ sr
             const int m0 = 8 * g;
             float v[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = !pad && m0 + e < d ? x[m0 + e] : 0.f;
+            for (int e = 0; e < 8; ++e) v[e] = !pad && m0 + e < d ? x[m0 + e] - mu[m0 + e] : 0.f;
             uint32_t hw[4], lw[4];
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -516,7 +517,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // 128, k = 56 take 1.5 ms and one of 2M x 256, k = 1000 with Dirichlet weights
 // 154 ms (now 24 ms), one of 400K x 128, k = 200 3.5 ms (now 0.35 ms).
 //
-// Error bounds (x and c the float32 row and centroid).  What decides between
+// Error bounds (x and c the float32 row and centroid, less mu).  What decides between
 // centroids is |c|^2 - 2 x.c (a row's own norm shifts all of them alike):
 //   - the split product: dropping lo.lo and the residuals of the two
 //     roundings costs at most 3.04 2^-16 |x_m| |c_m| per dimension;
@@ -530,7 +531,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 //   - |c|^2 summed in float32: (d / 64 + 16) 2^-24 |c|^2 (lanes share the
 //     dimensions), at most (d + 8) 2^-24 |c|^2; two additions and the norm's
 //     rounding at the magnitude of the values: 4 2^-24 R^2, R = |x| + max |c|;
-//   so a value is within e = (d + 8) 2^-24 max |c|^2 + 4 2^-24 R^2 +
+//     the roundings of row - mu and centroid - mu, 2^-24 of each, move the
+//     squared distance by 2 2^-24 R^2;
+//   so a value is within e = (d + 8) 2^-24 max |c|^2 + 6 2^-24 R^2 +
 //   2 (778 + 6.9 d') 2^-24 |x| max |c| of the row's common offset, plus an
 //   absolute 2^-100 (1 + R) for bf16 values below the normal range.
 // The packed key lowers a value v by less than 2^-15 of itself: the key of
@@ -670,7 +673,7 @@ __global__ __launch_bounds__(256) void k_refine_large(Dev P, Large Lg) {
         const float T0 = __uint_as_float(k0 & ~255u);
         const float xn = sqrtf(fmaxf(x2, 0.f)) * kUp;
         const float R = xn + cnmax;
-        const float e1 = (gexp * cnmax * cnmax + 0x1p-22f * R * R + gsp2 * xn * cnmax + 4.f * R * ecm +
+        const float e1 = (gexp * cnmax * cnmax + 0x1.8p-22f * R * R + gsp2 * xn * cnmax + 4.f * R * ecm +
                           2.f * ecm * ecm + 0x1p-100f * (1.f + R)) * kUp;
         const float thr = (T0 * (1.f + 0x1.1p-15f) + 2.f * e1) * kUp;
         // Only centroids whose expanded distance lies within thr of the
@@ -1331,7 +1334,10 @@ __global__ __launch_bounds__(256) void k_centroid_table_tiled(Dev P, Large Lg, i
         const int i = min(i0 + sr, k - 1);
         const float* c32 = P.C32 + (int64_t)i * d;
         double n2 = 0.0;
-        for (int m = sm; m < d; m += 16) n2 = fma((double)c32[m], (double)c32[m], n2);
+        for (int m = sm; m < d; m += 16) {
+            const double v = (double)c32[m] - (double)P.mu[m];
+            n2 = fma(v, v, n2);
+        }
 #pragma unroll
         for (int off = 8; off > 0; off >>= 1) n2 += __shfl_xor(n2, off);
         if (sm == 0 && i0 + sr < k) P.cn2[i] = (float)n2;
@@ -1366,7 +1372,7 @@ hipError_t launch_large_split_x(const Dev& dv, const Large& lg, int cus, hipStre
     if (g > (int64_t)cus * 16) g = (int64_t)cus * 16;
     hipLaunchKernelGGL(k_split_rows, dim3((unsigned)g), dim3(256), 0, s, dv.X, dv.n, dv.n, dv.d, lg.nch, lg.xs,
                        lg.x2, static_cast<const IterState*>(nullptr), 1, static_cast<const float*>(nullptr),
-                       static_cast<float*>(nullptr));
+                       static_cast<float*>(nullptr), static_cast<const float*>(dv.mu));
     return hipGetLastError();
 }
 
@@ -1399,7 +1405,7 @@ hipError_t launch_large_table(const Dev& dv, const Large& lg, int force, hipStre
     const int64_t kp = (int64_t)lg.nct * kLgN;   // padded to whole centroid tiles
     hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((kp + 3) / 4)), dim3(256), 0, s, static_cast<const float*>(dv.C32),
                        kp, (int64_t)dv.k, dv.d, lg.nch, lg.cs, lg.cn2p, static_cast<const IterState*>(dv.st), force,
-                       static_cast<const float*>(lg.smin), dv.s);
+                       static_cast<const float*>(lg.smin), dv.s, static_cast<const float*>(dv.mu));
     return hipGetLastError();
 }
 

@@ -315,3 +315,23 @@ def test_many_candidates_of_duplicate_rows(d, k, distinct):
             ref = oracle.lloyd(X * np.float32(scale), C0 * np.float32(scale), 6)
             check_assign(a.cpu().numpy(), ref["assign"], ref["best"], ref["second"])
             check_centroids(c.cpu().numpy(), ref["C"], X * np.float32(scale))
+
+
+@pytest.mark.parametrize("n,d,k", [(3000, 3, 100), (4001, 17, 33), (3000, 40, 70), (2500, 65, 200), (3000, 6, 300),
+                                   (2000, 150, 260)])
+def test_data_far_from_the_origin(n, d, k):
+    # the split products are formed relative to the centroids' mean there
+    X, C0 = synth.blobs(n, d, k, seed=931 + d, spread=4.0, sigma=1.5, comps=max(1, k // 3))
+    rng = np.random.default_rng(931 + d)
+    far = rng.normal(0.0, 400.0, d).astype(np.float32)
+    X, C0 = X + far, C0 + far
+    X[7] = 0.0                                # far from every centroid
+    a, c, st = km.run(_gpu(X), _gpu(C0), 8)
+    b, e, s2 = km.run(_gpu(X), _gpu(C0), 8, generic=True) if d * k < 5000 else (a, c, st)
+    assert torch.equal(a, b) and torch.equal(c.view(torch.int32), e.view(torch.int32))
+    ref = oracle.lloyd(X, C0, 8)
+    assert st["iterations"] == ref["iters"]
+    check_assign(a.cpu().numpy(), ref["assign"], ref["best"], ref["second"])
+    check_centroids(c.cpu().numpy(), ref["C"], X)
+    # float64 decisions are near ties alone, not every survivor
+    assert st["rechecks"] < 0.05 * n * st["iterations"]
