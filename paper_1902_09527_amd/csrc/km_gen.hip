@@ -679,7 +679,7 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
             // of lanes its own time: they meet near this many rows (1 to 10
             // dimensions, 65 to 256 centroids; with a quarter of them 5000 x 1,
             // k = 200 took 1.33 times as long, 20K x 6, k = 200 1.41 times).
-            if (d <= kGenLaneD && __popcll(am) > 4 + k * (d + 10) / 100) {
+            if (__builtin_expect(d <= kGenLaneD && __popcll(am) > 4 + k * (d + 10) / 100, 0)) {
                 const float* xr = P.X + (int64_t)p * d;
                 float x[kGenLaneD];
 #pragma unroll
@@ -759,7 +759,7 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
         // dimensions in order by one lane as on the other paths: rows at equal
         // distances from two centroids then fall alike on all of them.
         if (d <= kGenLaneD) {   // a lane per row
-            if (re) {
+            if (__builtin_expect(re, 0)) {
                 const float* xr = P.X + (int64_t)p * d;
                 double Dbb = INFINITY;
                 int kb = INT_MAX, bb = -1;
@@ -903,7 +903,7 @@ __global__ __launch_bounds__(64 * gen_mat_waves(KB, ONE)) __attribute__((amdgpu_
                         v[4 * c + 2] = t.z * xsc;
                         v[4 * c + 3] = t.w * xsc;
                     }
-                    if (shift && (q == 0 || both)) {   // uniform
+                    if (__builtin_expect(shift && (q == 0 || both), 0)) {   // uniform
                         const float* mp = P.mu + 16 * (s0 + i + q) + 8 * half;
 #pragma unroll
                         for (int e = 0; e < 8; ++e) v[e] = fmaf(A.v[2 * (i + q) + e / 4][e % 4], xsc, -(mp[e] * xsc));

@@ -159,7 +159,8 @@ __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ sr
                                                     int nch, uint32_t* __restrict__ dst, float* __restrict__ norms,
                                                     const IterState* st, int force, const float* __restrict__ smin,
                                                     float* __restrict__ s_out, const float* __restrict__ mu) {
-    if (st && !force && !st->active) return;
+    if (!force && !st->active) return;
+    const bool shift = st->shift != 0;
     const int lane = threadIdx.x & 63;
     const int64_t wstride = (int64_t)gridDim.x * (blockDim.x >> 6);
     for (int64_t r = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); r < rows; r += wstride) {
@@ -171,7 +172,11 @@ __global__ __launch_bounds__(256) void k_split_rows(const float* __restrict__ sr
             const int m0 = 8 * g;
             float v[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = !pad && m0 + e < d ? x[m0 + e] - mu[m0 + e] : 0.f;
+            for (int e = 0; e < 8; ++e) v[e] = !pad && m0 + e < d ? x[m0 + e] : 0.f;
+            if (shift) {   // uniform
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = !pad ? v[e] - mu[m0 + e] : 0.f;   // (mu is zero past d)
+            }
             uint32_t hw[4], lw[4];
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -1371,7 +1376,7 @@ hipError_t launch_large_split_x(const Dev& dv, const Large& lg, int cus, hipStre
     int64_t g = (dv.n + 3) / 4;
     if (g > (int64_t)cus * 16) g = (int64_t)cus * 16;
     hipLaunchKernelGGL(k_split_rows, dim3((unsigned)g), dim3(256), 0, s, dv.X, dv.n, dv.n, dv.d, lg.nch, lg.xs,
-                       lg.x2, static_cast<const IterState*>(nullptr), 1, static_cast<const float*>(nullptr),
+                       lg.x2, static_cast<const IterState*>(dv.st), 1, static_cast<const float*>(nullptr),
                        static_cast<float*>(nullptr), static_cast<const float*>(dv.mu));
     return hipGetLastError();
 }
