@@ -29,7 +29,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 MFMA_F32_PEAK_TFS = 157.3   # MI355X dense float32 matrix peak
-MFMA_BF16_PEAK_TFS = 2500.0  # MI355X dense bf16 matrix peak (the split products of k_mfma_large, k_inc_mat)
+MFMA_BF16_PEAK_TFS = 2500.0  # MI355X dense bf16 and f16 matrix peak (the split products of k_mfma_large, k_inc_mat)
 DEFAULT_WORKLOAD = "aniso-8M-d16-k10"
 METRIC = "k-means iters/sec + effective dist evals/sec; % HBM peak (low d) / % MFMA (big k·d)"
 
@@ -41,6 +41,7 @@ def log(msg: str) -> None:
 # Dominant (assignment-step) kernel of each library path.
 DOMINANT_KERNEL = {"stream-d16": "k_inc", "stream-d16-full": "k_small", "lds-vector": "k_assign",
                    "lds-mfma": "k_assign", "lds-elkan": "k_assign", "lds-inc": "k_inc_mat",
+                   "lds-inc-vec": "k_inc_vec",
                    "global-mfma": "k_mfma_large"}
 # Sources of each dominant kernel: the hardware byte counts of a committed
 # profile summary are used only while these files are unchanged.
@@ -51,6 +52,7 @@ KERNEL_SOURCES = {
     "k_first": ["km_small.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
     "k_assign": ["km_kernels.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
     "k_inc_mat": ["km_gen.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
+    "k_inc_vec": ["km_gen.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
     "k_mfma_large": ["km_large.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
     "k_pp_step": ["km_pp.hip", "km_device.h", "km_internal.h", "km_capi.hip"],
 }
@@ -410,7 +412,7 @@ def main() -> int:
         # read and written (12 B) plus, with incremental sums, the rows of the
         # Clause-1 survivors and of the changed points (4d B each), or with
         # full sums every row (4d B) and the changed assignments (4 B).
-        if path in ("stream-d16", "lds-inc"):
+        if path in ("stream-d16", "lds-inc", "lds-inc-vec"):
             bytes_per_launch = 12.0 * n + 4.0 * d * (surv + ch) / m
             what = "steps 1..T-1: 12n (assignment, bound) + 4d per Clause-1 survivor and per changed point"
         elif path == "lds-elkan":
@@ -437,9 +439,9 @@ def main() -> int:
             if path == "lds-inc":
                 rooflines.append(mfma_roofline_entry(kernel, tag, flops, launch_ms,
                                                      "steps 1..T-1: 2*d per distance of the evaluated "
-                                                     "32-centroid blocks; the matrix cores run 3 bf16 "
+                                                     "32-centroid blocks; the matrix cores run 3 f16 "
                                                      "products per dot (3x these flops)", MFMA_BF16_PEAK_TFS,
-                                                     "bf16"))
+                                                     "f16"))
         if path == "stream-d16":   # the full-read streaming kernel on the same steps
             _, later_f, h_f = kernel_pass(KS, **dict(base_flags, full_sums=True))
             ch_f = int(h_f["changed"][1:KS].sum())

@@ -197,19 +197,19 @@ int kmeans_mti_run(const float* X, int64_t n, int32_t d, int32_t k, const float*
  * before it; the one-block update k_small_finish runs after k_small and
  * before results are read), "stream-d16-full" (k_small every step, each
  * followed by k_small_finish, with KM_FLAG_FULL_SUMS or KM_FLAG_STATS),
- * "lds-vector" /
- * "lds-mfma" (centroids and sums in LDS: k_assign with vector or matrix-core
- * survivors, then k_reduce, k_update, k_centroid_table; "lds-vector" without
- * a flag that asks for the general kernel or for full sums is k_inc_vec,
- * d <= 16 and few centroids: only the point states and the Clause-1
- * survivors' rows are read, one lane per survivor; then k_update,
- * k_centroid_table), "lds-inc" (only the states and the survivors' rows are
- * read, the survivors are settled on the matrix cores and the moves of the
- * points whose cluster changed are summed: k_inc_mat, k <= 256 while its tables
- * fit in LDS, then k_update, k_centroid_table; with KM_FLAG_STATS reported as
- * "lds-mfma" for d = 16 or 32 and 16 < k <= 128), "lds-elkan" (the general
- * kernel with KM_FLAG_ELKAN's lower-bound scan), "global-mfma"
- * (centroids or sums too large for LDS: dense MFMA survivors, sums by
+ * "lds-inc-vec" (d <= 16 and few centroids: k_inc_vec reads the point states
+ * and only the Clause-1 survivors' rows, settles a survivor per lane and moves
+ * the sums of the points whose cluster changed; k_gen_finish ends the step),
+ * "lds-inc" (the same with the survivors settled on the matrix cores,
+ * k_inc_mat, any d and k <= 256 while its tables fit in LDS; k_gen_finish, or
+ * k_update and k_centroid_table), "lds-vector" / "lds-mfma" (centroids and
+ * sums in LDS, every row read in every step: k_assign with vector or
+ * matrix-core survivors, then k_reduce, k_update, k_centroid_table; with a
+ * flag that asks for it, and where no other path applies: k <= 256 whose
+ * tables are too large for k_inc_mat's LDS, for instance d = 128 and k = 65
+ * to 82, and some shapes of few dimensions and more centroids), "lds-elkan"
+ * (the general kernel with KM_FLAG_ELKAN's lower-bound scan), "global-mfma"
+ * (more than 256 centroids, or tables too large for LDS: dense MFMA survivors, sums by
  * counting sort).  "" for a NULL context.
  */
 const char* kmeans_mti_path(const km_ctx* ctx);

@@ -1361,11 +1361,8 @@ const char* kmeans_mti_path(const km_ctx* ctx) {
     if (!ctx) return "";
     if (ctx->small) return ctx->inc ? "stream-d16" : "stream-d16-full";
     if (ctx->large) return "global-mfma";
-    if ((ctx->flags & KM_FLAG_STATS) && ctx->gen == km::kGenMat && ctx->k > 16 && ctx->k <= 128 &&
-        (ctx->d == 16 || ctx->d == 32))
-        return "lds-mfma";
     if (ctx->gen == km::kGenMat) return "lds-inc";
-    if (ctx->gen == km::kGenVec) return "lds-vector";
+    if (ctx->gen == km::kGenVec) return "lds-inc-vec";
     if (ctx->variant % 16 == 8) return "lds-elkan";
     return ctx->variant % 16 ? "lds-mfma" : "lds-vector";
 }

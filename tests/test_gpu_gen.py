@@ -1,4 +1,4 @@
-"""The general incremental steps (any d; one lane per survivor on "lds-vector",
+"""The general incremental steps (any d; one lane per survivor on "lds-inc-vec",
 matrix cores on "lds-inc") on the GPU.
 
 KM_FLAG_FULL_SUMS takes the same problem through the general assignment kernel
@@ -38,9 +38,9 @@ def _same(Xg, Cg, iters, **kw):
 
 CASES = [
     # n, d, k, path
-    (1000, 1, 5, "lds-vector"), (63, 3, 7, "lds-vector"), (64 * 5 + 1, 4, 64, "lds-vector"),
-    (3000, 4, 65, "lds-inc"), (5000, 8, 32, "lds-vector"), (5000, 8, 33, "lds-inc"),
-    (2000, 12, 21, "lds-vector"), (2001, 12, 22, "lds-inc"), (700, 10, 1, "lds-vector"),
+    (1000, 1, 5, "lds-inc-vec"), (63, 3, 7, "lds-inc-vec"), (64 * 5 + 1, 4, 64, "lds-inc-vec"),
+    (3000, 4, 65, "lds-inc"), (5000, 8, 32, "lds-inc-vec"), (5000, 8, 33, "lds-inc"),
+    (2000, 12, 21, "lds-inc-vec"), (2001, 12, 22, "lds-inc"), (700, 10, 1, "lds-inc-vec"),
     (4097, 15, 32, "lds-inc"), (4096, 17, 33, "lds-inc"), (300000 + 7, 20, 64, "lds-inc"),
     (3001, 31, 65, "lds-inc"), (3000, 33, 100, "lds-inc"), (6000, 48, 128, "lds-inc"),
     (2500, 63, 30, "lds-inc"), (2500, 64, 31, "lds-inc"), (2500, 65, 40, "lds-inc"),

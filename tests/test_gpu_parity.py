@@ -199,20 +199,21 @@ def test_determinism_bitwise():
 # rounded down), and through the bounds those points then carry.  Slack per
 # step: 0.2 % of n points for Clause 1, 0.2 % of n * k for computed distances.
 COUNTER_CASES = [
-    # seed, n, d, k, spread, sigma, iters, flags
-    (91, 200000, 32, 100, 20.0, 1.5, 12, {"vector_only": True}),
-    (92, 150000, 16, 24, 6.0, 1.5, 12, {"vector_only": True}),
-    (93, 120000, 5, 30, 5.0, 1.0, 12, {}),
+    # seed, n, d, k, spread, sigma, iters, flags, path
+    (91, 200000, 32, 100, 20.0, 1.5, 12, {"vector_only": True}, "lds-vector"),
+    (92, 150000, 16, 24, 6.0, 1.5, 12, {"vector_only": True}, "lds-vector"),
+    (93, 120000, 5, 30, 5.0, 1.0, 12, {}, "lds-inc-vec"),
+    (93, 120000, 5, 30, 5.0, 1.0, 12, {"generic": True}, "lds-vector"),
 ]
 
 
-@pytest.mark.parametrize("case", COUNTER_CASES, ids=lambda c: "s%d-n%d-d%d-k%d" % c[:4])
+@pytest.mark.parametrize("case", COUNTER_CASES, ids=lambda c: "s%d-n%d-d%d-k%d-%s" % (c[:4] + c[8:]))
 def test_prune_counters_match_the_mti_reference(case):
-    seed, n, d, k, spread, sigma, iters, flags = case
+    seed, n, d, k, spread, sigma, iters, flags, path = case
     X, C0 = synth.blobs(n, d, k, seed=seed, spread=spread, sigma=sigma)
     ref = oracle.mti(X, C0, iters)
     with km.KMeansMTI(_gpu(X), _gpu(C0), **flags) as ctx:
-        assert ctx.path() == "lds-vector"
+        assert ctx.path() == path
         for _ in range(iters):
             ctx.iterate()
         h = ctx.history()

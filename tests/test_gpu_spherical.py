@@ -37,16 +37,18 @@ CASES = [
     (201, 5000 + 3, 16, 10, 3.0, 1.0, 20, 0.0, {}, "stream-d16"),
     (202, 40000 + 11, 16, 16, 2.0, 1.5, 25, 0.0, {}, "stream-d16"),
     (203, 20000 + 7, 16, 7, 3.0, 1.0, 20, 0.001, {"stats": True}, "stream-d16-full"),
-    (204, 3000 + 1, 5, 7, 3.0, 1.0, 25, 0.0, {"stats": True}, "lds-vector"),
-    (205, 6000 + 5, 32, 40, 4.0, 2.0, 20, 0.0, {"stats": True}, "lds-mfma"),
+    (204, 3000 + 1, 5, 7, 3.0, 1.0, 25, 0.0, {"stats": True}, "lds-inc-vec"),
+    (205, 6000 + 5, 32, 40, 4.0, 2.0, 20, 0.0, {"stats": True}, "lds-inc"),
     (206, 5000, 64, 200, 6.0, 2.0, 12, 0.0, {"stats": True}, "global-mfma"),
     (207, 4000 + 3, 64, 50, 3.0, 1.0, 10, 0.0, {"large_path": True, "stats": True}, "global-mfma"),
     (208, 3000, 16, 12, 3.0, 1.0, 15, 0.0, {"generic": True, "stats": True}, "lds-vector"),
+    (204, 3000 + 1, 5, 7, 3.0, 1.0, 25, 0.0, {"generic": True, "stats": True}, "lds-vector"),
+    (205, 6000 + 5, 32, 40, 4.0, 2.0, 20, 0.0, {"generic": True, "stats": True}, "lds-mfma"),
     (209, 6000 + 5, 32, 40, 4.0, 2.0, 20, 0.0, {}, "lds-inc"),
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "s%d-n%d-d%d-k%d" % c[:4])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "s%d-n%d-d%d-k%d-%s" % (c[:4] + c[9:]))
 def test_spherical_matches_oracle(case):
     seed, n, d, k, spread, sigma, iters, tol, flags, path = case
     print("case", case[:8], flags, flush=True)
