@@ -335,3 +335,21 @@ def test_data_far_from_the_origin(n, d, k):
     check_centroids(c.cpu().numpy(), ref["C"], X)
     # float64 decisions are near ties alone, not every survivor
     assert st["rechecks"] < 0.05 * n * st["iterations"]
+
+
+@pytest.mark.parametrize("n,d,k", [(1_300_001, 3, 7), (4_700_003, 5, 7), (700_001, 12, 21), (2_300_017, 8, 10),
+                                   (600_007, 40, 20), (1_200_001, 40, 60), (1_200_001, 40, 100), (700_001, 40, 200),
+                                   (1_200_003, 24, 20), (900_001, 9, 200)], ids=lambda v: str(v))
+def test_waves_of_many_tiles_match_the_full_read_path(n, d, k):
+    # sizes at which a wave takes two or four sub-steps a tile and several tiles
+    # from the block's counter, its queue carried from one to the next; the last
+    # tile is short
+    g = torch.Generator(device=DEV)
+    g.manual_seed(941 + d + k)
+    m = torch.randn(k, d, generator=g, device=DEV) * 3
+    X = (m[torch.randint(k, (n,), generator=g, device=DEV)] + torch.randn(n, d, generator=g, device=DEV)).contiguous()
+    C0 = X[torch.randperm(n, generator=g, device=DEV)[:k]].contiguous()
+    with km.KMeansMTI(X, C0) as ctx:
+        assert ctx.path() in ("lds-inc-vec", "lds-inc")
+    _, _, st = _same(X, C0, 5)
+    assert st["clause1_skips"] > 0
