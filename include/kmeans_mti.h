@@ -112,12 +112,14 @@ typedef struct {
     int32_t iterations;        /* assignment steps executed */
     int32_t converged;         /* run only: 1 if it stopped on the tol test before max_iters */
     int64_t changed_last;      /* points whose assignment changed in the last step */
-    int64_t dist_computed;     /* float32 point-centroid distances evaluated, tightenings included */
+    int64_t dist_computed;     /* point-centroid distances evaluated, tightenings included (matrix-core paths: all whose
+                                  products are formed) */
     int64_t dist_lloyd;        /* n * k * iterations: what unpruned Lloyd's evaluates */
     int64_t clause1_skips;     /* point-iterations skipped whole by Clause 1 */
     int64_t rechecks;          /* points decided again in float64 (near ties) */
     double inertia_last;       /* last step's inertia (where every row is read float32 distances summed exactly, else
-                                  from the exact per-cluster sums and the sum of |x|^2); NaN without KM_FLAG_STATS */
+                                  from the exact per-cluster sums and the sum of |x|^2, within about 2^(log2 n - 56) d
+                                  max|x| max|c| a row); NaN without KM_FLAG_STATS */
     double device_ms;          /* run only: device time of the iteration loop (HIP events); else 0 */
 } km_stats;
 

@@ -149,7 +149,7 @@ __device__ __forceinline__ void flush_block(const Dev& P, const uint64_t* acc, c
 // survivors at a time).  Four centroids are formed side by side, since one
 // after another each waited for the bound and the table entry of the one
 // before.  The general kernel, which it replaces here, read and summed every
-// row in every step: 66M x 8, k = 10 took 3.27 ms a step and takes 0.5 ms
+// row in every step: 66M x 8, k = 10 took 3.27 ms a step and takes 0.59 ms
 // (the survivors' lines and the states are 0.5 ms at 4.8 TB/s).
 
 template <int DP>

@@ -117,10 +117,12 @@ def test_general_step_with_infinite_and_nan_rows_ends():
                                       (2000, 33, 300, {}), (3000, 24, 20, {"spherical": True}), (300, 20, 300, {})],
                          ids=lambda v: str(v))
 def test_inertia_from_exact_sums(n, d, k, kw):
-    # sum |x|^2 + sum_j (n_j |c_j|^2 - 2 c_j . S_j): the sums are exact images
-    # within 2^-50 of max |x| per value, everything else is carried in double
-    # pairs, so the inertia is within about 2^-48 of sum |x|^2 (1e-12 of it
-    # here; sum |x|^2 is below 100 times the inertia for k << n).
+    # sum |x|^2 + sum_j (n_j |c_j|^2 - 2 c_j . S_j): a value's image is within
+    # 2^(log2 n - 57) max |x| (the scale leaves log2 n bits to the sums and four to
+    # values outside the sample): 2^-45 of max |x| at 3000 rows, and values above
+    # 2^-20 of max |x| are exact.  Everything else is carried in double pairs, so
+    # the inertia is within about 2^-43 of sum |x|^2 (1e-12 of it here; sum |x|^2
+    # is below 100 times the inertia for k << n).
     X, C0 = synth.blobs(n, d, k, seed=841 + d, spread=4.0, sigma=1.5, comps=min(k, 30))
     if k == n:
         C0 = X.copy()
