@@ -396,8 +396,10 @@ int enqueue_iteration(km_ctx* c) {
     int first = c->gen && c->enq == 0 ? 1 : 0, check = 0;
     if (first) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if ((e = hipStreamIsCapturing(c->stream, &cap)) != hipSuccess)
-            return fail_ctx(c, hip_fail(e, "hipStreamIsCapturing"));
+        if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {   // not a stream that is recorded
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusNone;
+        }
         if (cap == hipStreamCaptureStatusActive) {
             e = km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, 1, 1, c->stream);
             if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "assign kernel"));
