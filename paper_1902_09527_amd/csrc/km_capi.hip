@@ -470,14 +470,15 @@ int read_state(km_ctx* c, km::IterState* out) {
 //   - one column with more than 10 rows a centroid: hundreds of centroids on a
 //     line lie closer than the split products tell apart, so that most
 //     survivors have many candidates (50K x 1, k = 500 196 us a step there, 280 on
-//     the global path; 2716 x 1, k = 282 101 and 81);
+//     the global path; 2716 x 1, k = 282 101 and 81); with spherical k-means two
+//     columns are such a line (139K x 2, k = 355 155 and 292);
 //   - many rows of few dimensions and not many more than 256 centroids: its
 //     scan, about k (2 d + 8) instructions a survivor, costs no more than the
 //     candidate lists (200K x 2, k = 260 145 and 222 us, 200K x 3, k = 260 173 and
 //     200; 200K x 4, k = 260 229 and 214, 200K x 3, k = 400 239 and 191).
-bool large_pays(int64_t n, int32_t d, int32_t k, int dev) {
+bool large_pays(int64_t n, int32_t d, int32_t k, bool sphere, int dev) {
     if (k <= km::kGenMatMaxK || d > km::kLgMaxD || k >= 0xffff) return false;
-    if (d == 1 && n > 10 * (int64_t)k) return false;
+    if (d <= (sphere ? 2 : 1) && n > 10 * (int64_t)k) return false;
     if (n > 100000 && (int64_t)k * (2 * d + 8) < 4000) return false;
     const double need = (double)n * (64.0 * km::split_chunks(d) + 64.0 * ((k + km::kLgN - 1) / km::kLgN) + 60.0);
     if (n > INT_MAX || need > 64.0 * (1 << 30)) return false;
@@ -617,7 +618,7 @@ int init_impl(km_ctx* c, const float* X, int64_t n, int32_t d, int32_t k, const 
         // although the general kernel's tables fit in LDS.
         if (c->tp > 0 && !elkan &&
             !(c->flags & (KM_FLAG_GENERIC | KM_FLAG_VECTOR_ONLY | KM_FLAG_FULL_SUMS | KM_FLAG_NO_PRUNE)) &&
-            large_pays(n, d, k, c->device))
+            large_pays(n, d, k, (c->flags & KM_FLAG_SPHERICAL) != 0, c->device))
             c->tp = 0;
     }
     if (c->small || c->gen) {

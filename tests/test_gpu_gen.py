@@ -355,3 +355,12 @@ def test_waves_of_many_tiles_match_the_full_read_path(n, d, k):
         assert ctx.path() in ("lds-inc-vec", "lds-inc")
     _, _, st = _same(X, C0, 5)
     assert st["clause1_skips"] > 0
+
+
+def test_two_columns_on_the_sphere_are_a_line():
+    X, C0 = synth.blobs(4000, 2, 300, seed=951, spread=4.0, sigma=1.5)
+    Xg, Cg = _gpu(X), _gpu(C0 + np.float32(0.01))
+    for kw, path in (({"spherical": True}, "lds-vector"), ({}, "global-mfma")):
+        with km.KMeansMTI(Xg, Cg, **kw) as ctx:
+            assert ctx.path() == path
+        _same(Xg, Cg, 6, **kw)
