@@ -241,6 +241,7 @@ struct km_ctx {
     bool inc = false;     // ... with incremental steps after the first
     km::GenKind gen = km::kGenNone;   // general incremental step (any d)
     int gg = 0, gsub = 1, lds_gen = 0;   // its grid, 64-point sub-steps per wave tile and LDS
+    bool recorded = false;               // ... the first call was recorded into a graph
     int gi = 0, lds_inc = 0;   // grid and LDS of the incremental kernel
     int gf = 0, lds_first = 0;  // grid and LDS of the matrix-core first step (0: k_small runs it)
     bool fuse_scan = false;     // that first step also finds the largest |x| (no set-up scan of X)
@@ -391,8 +392,10 @@ int enqueue_iteration(km_ctx* c) {
         c->stepped = true;
         return KM_OK;
     }
-    // A first call that is recorded into a graph may be replayed as any step:
-    // both forms are recorded, and the loop state picks one at each replay.
+    // A first call that is recorded into a graph may be replayed as any step, or
+    // not at all before a later call: from there on every call launches both
+    // forms, and the loop state picks one.  (The other form would read point
+    // states that no step has written.)
     int first = c->gen && c->enq == 0 ? 1 : 0, check = 0;
     if (first) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -400,12 +403,13 @@ int enqueue_iteration(km_ctx* c) {
             (void)hipGetLastError();
             cap = hipStreamCaptureStatusNone;
         }
-        if (cap == hipStreamCaptureStatusActive) {
-            e = km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, 1, 1, c->stream);
-            if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "assign kernel"));
-            first = 0;
-            check = 1;
-        }
+        c->recorded = cap == hipStreamCaptureStatusActive;
+    }
+    if (c->recorded) {
+        e = km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, 1, 1, c->stream);
+        if (e != hipSuccess) return fail_ctx(c, hip_fail(e, "assign kernel"));
+        first = 0;
+        check = 1;
     }
     e = c->gen     ? km::launch_gen(c->gen, c->dv, c->gg, c->gsub, c->lds_gen, first, check, c->stream)
         : c->large ? km::launch_large_assign(c->dv, c->lg, c->gb, c->stream)

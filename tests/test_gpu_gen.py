@@ -154,7 +154,8 @@ def test_shapes_of_different_lds_need_alternate_on_one_kernel():
 
 
 @pytest.mark.parametrize("n,d,k,large", [(16000, 6, 138, False), (12000, 5, 60, False), (12000, 24, 60, False),
-                                         (6000, 40, 90, False), (21000, 17, 294, False), (9000, 6, 50, True)],
+                                         (6000, 40, 90, False), (21000, 17, 294, False), (9000, 6, 50, True),
+                                         (12000, 16, 12, False), (12000, 16, 40, False), (9000, 32, 100, True)],
                          ids=lambda v: str(v))
 def test_tied_rows_fall_alike_on_every_path(n, d, k, large):
     # whole numbers projected to the unit sphere: many rows at equal distances
@@ -190,6 +191,19 @@ def test_captured_step_replays_as_every_step(n, d, k, kw):
             s.synchronize()
             assert torch.equal(a, b) and torch.equal(c.view(torch.int32), e.view(torch.int32)), t
         assert ctx.stats()["iterations"] == 6 and ctx.stats()["dist_computed"] == ref.stats()["dist_computed"]
+        # recorded, and the next call made before any replay
+        with km.KMeansMTI(Xg, Cg, **kw) as late:
+            other = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(other, stream=s):
+                late.iterate()
+            for t in range(3):
+                late.iterate(sync=True)
+                other.replay()
+            s.synchronize()
+            a, c = late.get()
+            b, e = ref.get()
+            s.synchronize()
+            assert torch.equal(a, b) and torch.equal(c.view(torch.int32), e.view(torch.int32))
 
 
 @pytest.mark.parametrize("m", [2, 3, 5, 6, 7])
